@@ -21,6 +21,8 @@
 // derivative of the branch the forward step took. Gradients are accumulated in FP64.
 #pragma once
 
+#include <type_traits>
+
 #include "step_kernels.hpp"
 
 namespace lbm {
@@ -167,11 +169,12 @@ __device__ inline void cm_back_vjp(const R in[8], const R ld[19], R out[8]) {
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_adj_seed(StepArgs<P> A, typename Prec<P>::R* lout) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
-  const int t = fluid_tile(A) * kBlock + threadIdx.x;
-  if (t >= A.nfluid) return;
+  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.nfluid)) return;
   R a, b;
-  unpack_frac(ld4(A.ain, t).x, a, b);
+  unpack_frac(ld4<Off>(A.ain, t).x, a, b);
   R s = 0;
 #pragma unroll
   for (int i = 0; i < 19; ++i) {
@@ -190,28 +193,27 @@ __global__ __launch_bounds__(kBlock) void k_adj_seed(StepArgs<P> A, typename Pre
 template <int P>
 __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
-  const int t = fluid_tile(A) * kBlock + threadIdx.x;
+  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
   double gxi = 0.0;
-  const int n = (t < A.nfluid) ? A.fluid[t] : 0;
-  const uint32_t inf = (t < A.nfluid) ? A.finfo[t] : 0u;
-  if (inf & kFluid) {
-    const Nbr nb = make_nbr(n, A.geo);
+  if (t < uint32_t(A.nfluid)) {
+    const ListNode ln = ldx<Off>(A.fluid, t);
+    const int n = ln.node;
+    const uint32_t inf = ln.info;
+    const Nbr nb = make_nbr(n, inf, A.geo);
     // ---------------- forward recompute ----------------
     // The pull sources are needed again by the final scatter; they wait in LDS meanwhile.
-    __shared__ int sid_lds[18][kBlock];
-    int sid[18];
-    pull_sources_lean(A.fid, nb, t, inf, sid);
+    __shared__ uint32_t sid_lds[18][kBlock];
+    uint32_t sid[18];
+    pull_sources<Off>(A.ids, nb, t, inf, sid);
 #pragma unroll
     for (int i = 0; i < 18; ++i) sid_lds[i][threadIdx.x] = sid[i];
     R f[19];
 #pragma unroll
-    for (int i = 0; i < 19; ++i) {
-      const bool bb = (i < 18) && ((inf >> i) & 1u);
-      const int src = (i < 18) ? sid[i] : t;
-      const int q = bb ? D::opp[i] : i;
-      f[i] = Prec<P>::ld(A.fin[size_t(q) * A.ps + src], R(D::w(i)), A.inv_scale);
-    }
+    for (int i = 0; i < 18; ++i)
+      f[i] = Prec<P>::ld(ld_pull<Off>(A.fin, A.ps, i, D::opp[i], sid[i], inf), R(D::w(i)), A.inv_scale);
+    f[18] = Prec<P>::ld(ldx<Off>(A.fin + 18 * A.ps, t), R(D::w(18)), A.inv_scale);
     R rm = 0;
 #pragma unroll
     for (int i = 0; i < 19; ++i) rm += f[i];
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
     const R ux = mx * irm, uy = my * irm, uz = mz * irm;
     R rr, rp;
     rn_densities(A.rhoN[n], rm, rr, rp);
-    const typename V4<R>::T nsv = ld4(A.nst, t);
+    const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
     const R nn[3] = {nsv.x, nsv.y, nsv.z};
     const R glen = nsv.w;
     const bool has_n = glen > A.eps;
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
       R Jm[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
 #pragma unroll
       for (int i = 0; i < 18; ++i) {
-        const typename V4<R>::T mv = ld4(A.nst, sid[D::opp[i]]);  // own id where x + c_i is solid
+        const typename V4<R>::T mv = ld4<Off>(A.nst, sid[D::opp[i]]);  // own id where x + c_i is solid
         const R a0 = mv.x, a1 = mv.y, a2 = mv.z;
         const R w3 = R(3.0 * D::w(i));
         if (D::cx[i]) { Jm[0][0] += w3 * R(D::cx[i]) * a0; Jm[1][0] += w3 * R(D::cx[i]) * a1; Jm[2][0] += w3 * R(D::cx[i]) * a2; }
@@ -272,15 +274,11 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
     const bool inlet = A.species && (inf & kInlet);
     const bool outlet = A.species && (inf & kOutlet);
     if (A.species) {
+      const uint32_t ginf = outlet ? inf & ~2u : inf;  // zero-gradient outflow: the node's own S_1
 #pragma unroll
       for (int i = 0; i < 6; ++i) {
-        if (i == 1 && outlet) {
-          g[i] = ld_species(A, 1, t);
-        } else {
-          const bool bb = (inf >> i) & 1u;
-          const int q = bb ? D3Q7::opp[i] : i;
-          g[i] = ld_species(A, q, sid[i]);
-        }
+        const uint32_t src = (i == 1 && outlet) ? t : sid[i];
+        g[i] = species_value(A, i, src, ld_pull<Off>(A.gin, A.ps, i, D3Q7::opp[i], src, ginf));
       }
       g[6] = ld_species(A, 6, t);
       C = 0;
@@ -516,8 +514,8 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
       J.lout[size_t(kAdjG + 6) * A.ps + t] = l_g[6];
     }
     J.lrn[n] = l_rn;
-    st4(J.lng, t, l_n[0], l_n[1], l_n[2], l_glen);
-    st4(J.lHn, t, has_n ? l_H : R(0), nn[0], nn[1], nn[2]);
+    st4<Off>(J.lng, t, l_n[0], l_n[1], l_n[2], l_glen);
+    st4<Off>(J.lHn, t, has_n ? l_H : R(0), nn[0], nn[1], nn[2]);
   }
   double s5[5] = {gxi, 0, 0, 0, 0};
   block_reduce5(s5, J.partials);
@@ -529,26 +527,28 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_adj_normal(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
   // Workgroup 0 first finishes the xi sum of k_adj_collide and adds it to dL/dxi.
   if (blockIdx.x == 0) {
     reduce_partials(J.partials, J.nparts, J.sum);
     if (threadIdx.x == 0) *J.gxi += J.sum[0];
   }
-  const int t = fluid_tile(A) * kBlock + threadIdx.x;
-  if (t >= A.nfluid) return;
-  const int n = A.fluid[t];
-  const uint32_t inf = A.finfo[t];
-  const Nbr nb = make_nbr(n, A.geo);
+  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.nfluid)) return;
+  const ListNode ln = ldx<Off>(A.fluid, t);
+  const int n = ln.node;
+  const uint32_t inf = ln.info;
+  const Nbr nb = make_nbr(n, inf, A.geo);
   const size_t N = A.N;
   // Every load of this node's own entries is issued here, before any is needed, so that they
   // share one memory round trip with the neighbours' ids (the wetting entries are read at every
   // node and used only at wetting nodes): the forward normal pass's n* and |G|, the normal
   // before realignment, the wetting data, dL/dn* and dL/d|G|, and the running dL/dtheta.
-  const typename V4<R>::T nsv = ld4(A.nst, t);
-  const typename V4<R>::T rv = ld4(A.nraw, t);
-  const typename V4<R>::T wv = ld4(A.wet, t);
-  const typename V4<R>::T lgv = ld4(J.lng, t);
+  const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
+  const typename V4<R>::T rv = ld4<Off>(A.nraw, t);
+  const typename V4<R>::T wv = ld4<Off>(A.wet, t);
+  const typename V4<R>::T lgv = ld4<Off>(J.lng, t);
   const R lgl = lgv.w;
   const double gth0 = J.gtheta[n];
   R mu[3] = {lgv.x, lgv.y, lgv.z};
@@ -556,11 +556,11 @@ __global__ __launch_bounds__(kBlock) void k_adj_normal(StepArgs<P> A, AdjArgs<ty
   // dH(x)/dn*_a(y) = -3 w_i (c_ia - n_a(x) (n(x).c_i)). The fluid ids of all 18 neighbours
   // first, then one gather of (dL/dH, n*) each; a solid y - c_i reads this node's own entry
   // and is discarded.
-  int mid[18];
-  pull_sources_lean(A.fid, nb, t, inf, mid);
+  uint32_t mid[18];
+  pull_sources<Off>(A.ids, nb, t, inf, mid);
 #pragma unroll
   for (int i = 0; i < 18; ++i) {
-    const typename V4<R>::T qv = ld4(J.lHn, mid[i]);
+    const typename V4<R>::T qv = ld4<Off>(J.lHn, mid[i]);
     const R lh = qv.x, q0 = qv.y, q1 = qv.z, q2 = qv.w;
     const bool use = !((inf >> i) & 1u) && lh != R(0);
     const R cn = R(D::cx[i]) * q0 + R(D::cy[i]) * q1 + R(D::cz[i]) * q2;
@@ -620,6 +620,7 @@ template <int P, bool EXT>
 __device__ inline typename Prec<P>::R grad_transpose(const StepArgs<P>& A, const AdjArgs<typename Prec<P>::R>& J,
                                                      int n, uint32_t inf, const Nbr& nb) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
   const size_t N = A.N;
   // Every load is issued before any is used; a direction whose source is solid reads this
@@ -639,17 +640,21 @@ __device__ inline typename Prec<P>::R grad_transpose(const StepArgs<P>& A, const
     // Fluid y (bit i set: y - c_i is solid, read as y and discarded): each component plane with
     // one gather per row triple. A component is read where c_i has it, and at the row centres
     // whose x-neighbours need it.
-    auto plane = [&](const R* g, int a, R out[18]) {
-      row_shared<true>(nb, inf, g[n], [&](int i) {
-        const int c = a == 0 ? D::cx[i] : (a == 1 ? D::cy[i] : D::cz[i]);
-        const bool centre = D::cx[i] == 0 && (D::cy[i] == 0 || D::cz[i] == 0);
-        const bool need = c != 0 || (a == 0 && centre);
-        return need ? g[((inf >> i) & 1u) ? n : nb.at(-D::cx[i], -D::cy[i], -D::cz[i])] : R(0);
-      }, out);
+    auto plane = [&](const R* g, auto axis, R out[18]) {
+      constexpr int a = decltype(axis)::value;
+      row_shared<true>(inf, ldx<Off>(g, uint32_t(n)),
+                       [&](int i) { return uint32_t(((inf >> i) & 1u) ? n : nb.at(-D::cx[i], -D::cy[i], -D::cz[i])); },
+                       [&](uint32_t k) { return ldx<Off>(g, k); },
+                       [](int i) {
+                         const int c = a == 0 ? D::cx[i] : (a == 1 ? D::cy[i] : D::cz[i]);
+                         const bool centre = D::cx[i] == 0 && (D::cy[i] == 0 || D::cz[i] == 0);
+                         return c != 0 || (a == 0 && centre);
+                       },
+                       out);
     };
-    plane(J.lG, 0, gx);
-    plane(J.lG + N, 1, gy);
-    plane(J.lG + 2 * N, 2, gz);
+    plane(J.lG, std::integral_constant<int, 0>(), gx);
+    plane(J.lG + N, std::integral_constant<int, 1>(), gy);
+    plane(J.lG + 2 * N, std::integral_constant<int, 2>(), gz);
   }
   R s = 0;
 #pragma unroll
@@ -668,12 +673,14 @@ __device__ inline typename Prec<P>::R grad_transpose(const StepArgs<P>& A, const
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_adj_grad_ext(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
-  const int t = logical_block() * kBlock + threadIdx.x;
-  if (t >= A.next) return;
-  const int n = A.ext[t];
-  const uint32_t inf = A.einfo[t];
-  const Nbr nb = make_nbr(n, A.geo);
+  const uint32_t t = uint32_t(logical_block()) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.next)) return;
+  const ListNode ln = ldx<Off>(A.ext, t);
+  const int n = ln.node;
+  const uint32_t inf = ln.info;
+  const Nbr nb = make_nbr(n, inf, A.geo);
   const R s = grad_transpose<P, true>(A, J, n, inf, nb);
   R den = 0;  // > 0: a solid node on this list has a fluid neighbour
 #pragma unroll
@@ -689,12 +696,14 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad_ext(StepArgs<P> A, AdjArgs<
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_adj_colour(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
-  const int t = fluid_tile(A) * kBlock + threadIdx.x;
-  if (t >= A.nfluid) return;
-  const int n = A.fluid[t];
-  const uint32_t inf = A.finfo[t];
-  const Nbr nb = make_nbr(n, A.geo);
+  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.nfluid)) return;
+  const ListNode ln = ldx<Off>(A.fluid, t);
+  const int n = ln.node;
+  const uint32_t inf = ln.info;
+  const Nbr nb = make_nbr(n, inf, A.geo);
   // At a solid y the adjoint is stored already divided by den(y) (k_adj_grad_ext). Loads for all
   // directions first (a fluid z - c_j reads this node's own entry, discarded).
   R ly[18];
@@ -721,14 +730,16 @@ __global__ __launch_bounds__(kBlock) void k_adj_colour(StepArgs<P> A, AdjArgs<ty
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_adj_final(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
-  const int t = fluid_tile(A) * kBlock + threadIdx.x;
-  if (t >= A.nfluid) return;
-  const int n = A.fluid[t];
-  const uint32_t inf = A.finfo[t];
-  const Nbr nb = make_nbr(n, A.geo);
+  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.nfluid)) return;
+  const ListNode ln = ldx<Off>(A.fluid, t);
+  const int n = ln.node;
+  const uint32_t inf = ln.info;
+  const Nbr nb = make_nbr(n, inf, A.geo);
   R a, b;
-  unpack_frac(ld4(A.ain, t).x, a, b);
+  unpack_frac(ld4<Off>(A.ain, t).x, a, b);
   R la = 0, lv[3] = {0, 0, 0};
   // The readers' pairs: y + c_q is the neighbour y - c_opp(q); where it is solid the reader is y
   // itself (bounce-back), and y for the rest population.
@@ -736,8 +747,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_final(StepArgs<P> A, AdjArgs<typ
   const V2R* lr2 = reinterpret_cast<const V2R*>(J.lr2);
   const V2R own2 = lr2[n];
   V2R rdv[18];
-  row_shared<true>(nb, inf, own2,
-                   [&](int i) { return lr2[((inf >> i) & 1u) ? n : nb.at(-D::cx[i], -D::cy[i], -D::cz[i])]; }, rdv);
+  row_shared<true>(inf, own2,
+                   [&](int i) { return uint32_t(((inf >> i) & 1u) ? n : nb.at(-D::cx[i], -D::cy[i], -D::cz[i])); },
+                   [&](uint32_t k) { return ldx<Off>(lr2, k); }, [](int) { return true; }, rdv);
 #pragma unroll
   for (int q = 0; q < 19; ++q) {
     const V2R lv2 = (q == 18) ? own2 : rdv[D::opp[q]];

@@ -43,4 +43,9 @@ enum : uint32_t {
   kOutlet = 1u << 25,          // species outflow plane x = nx - 1
 };
 
+// Bits 26..31 of the info words of the launch lists (not of the per-node words): the node lies on the
+// face x = 0, x = nx - 1, y = 0, y = ny - 1, z = 0, z = nz - 1. Its neighbours' periodic offsets
+// follow from them without the node's coordinates.
+constexpr int kFaceShift = 26;
+
 }  // namespace lbm

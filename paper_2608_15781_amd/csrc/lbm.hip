@@ -39,11 +39,23 @@ size_t store_bytes(int precision) { return precision == LBM_FP64 ? 8 : (precisio
 size_t real_bytes(int precision) { return precision == LBM_FP64 ? 8 : 4; }
 
 struct Layout {
-  size_t info, wet, rhoN, nst, state[2], partials, ring, lists[2], linfo[2], fid, counts, order, total;
+  size_t info, wet, rhoN, nst, state[2], partials, ring, lists[2], ids, counts, order, total;
   size_t f_off, a_off, g_off, c_off, state_bytes;  // within one state buffer
   size_t ps;  // elements between consecutive state (and adjoint) planes
   int nblocks;  // one thread per node, rounded up to a multiple of kXcd workgroups
 };
+
+size_t plane_stride(const lbm_params& p);
+
+// Whether some byte offset that the kernels form passes 32 bits. The largest are a population of the
+// pair's upper plane (the two planes of a pair are at most five apart, ld_pull), the 4-vectors per
+// fluid id, the pairs per node and the launch lists. FP32 lattices of up to 178 million fluid nodes
+// and FP64 ones of up to 89 million stay within them. On the 512^3 porous mask the 32-bit offsets
+// take a tenth off the instructions of the colour and collide passes.
+bool use_wide_offsets(const lbm_params& p) {
+  const size_t N = size_t(p.nx) * p.ny * p.nz, ps = plane_stride(p), s = store_bytes(p.precision), r = real_bytes(p.precision);
+  return std::max(std::max(6 * s * ps, 4 * r * ps), std::max(2 * r * N, sizeof(ListNode) * N)) >= (size_t(1) << 32);
+}
 
 // Upper bounds of the two launch lists: the fluid nodes (params.fluid_nodes when given, else
 // every node) and the solid nodes next to fluid (at most the solid nodes).
@@ -96,11 +108,9 @@ Layout make_layout(const lbm_params& p) {
   L.nst = o; o = align_up(o + 4 * r * F);   // per fluid id
   L.partials = o; o = align_up(o + 5 * sizeof(double) * size_t(nb));
   L.ring = o; o = align_up(o + 5 * sizeof(double) * kRing);
-  L.lists[0] = o; o = align_up(o + 4 * F);  // fluid nodes
-  L.lists[1] = o; o = align_up(o + 4 * E);  // solid nodes with extrapolated colour
-  L.linfo[0] = o; o = align_up(o + 4 * F);  // info words of the list entries
-  L.linfo[1] = o; o = align_up(o + 4 * E);
-  L.fid = o; o = align_up(o + 4 * N);       // node -> fluid id
+  L.lists[0] = o; o = align_up(o + sizeof(ListNode) * F);  // fluid nodes
+  L.lists[1] = o; o = align_up(o + sizeof(ListNode) * E);  // solid nodes with extrapolated colour
+  L.ids = o; o = align_up(o + sizeof(IdWord) * ((N + 31) / 32));  // node -> fluid id
   L.counts = o; o = align_up(o + 4 * (size_t(nb) + 2));
   L.order = o; o = align_up(o + 4 * size_t(nb));  // launch order of the fluid-list tiles
   L.state[0] = o; o = align_up(o + L.state_bytes);
@@ -160,6 +170,7 @@ AdjLayout make_adj_layout(const lbm_params& p) {
 
 struct lbm_ctx {
   lbm_params p;
+  int mode;  // the kernels' storage mode: p.precision, plus kWideMode where 32-bit byte offsets do not suffice
   int N;
   Layout L;
   char* ws;
@@ -300,8 +311,8 @@ __global__ void k_init_info(int nx, int ny, int nz, const uint8_t* solid, const 
 // sum is accumulated exactly in integers (5040 w = 448, 240, 96, 50, 16, 8, 1) and normalised
 // once; a zero sum leaves n_s undefined (stored as 0). Also stores cos(theta).
 template <class R>
-__global__ void k_init_wet(int nx, int ny, int nz, const uint8_t* solid, const uint32_t* info, const int* fid,
-                           const double* theta, double theta_uniform, R* wet) {
+__global__ void k_init_wet(int nx, int ny, int nz, const uint8_t* solid, const uint32_t* info,
+                           const IdWord* ids, const double* theta, double theta_uniform, R* wet) {
   const int n = blockIdx.x * blockDim.x + threadIdx.x;
   const int N = nx * ny * nz;
   if (n >= N || !(info[n] & kFluid)) return;
@@ -331,20 +342,19 @@ __global__ void k_init_wet(int nx, int ny, int nz, const uint8_t* solid, const u
   }
   double len = sqrt(double(sx * sx + sy * sy + sz * sz));
   double il = len > 0 ? 1.0 / len : 0.0;
-  st4(wet, fid[n], R(sx * il), R(sy * il), R(sz * il), R(cos(th)));
+  st4<size_t>(wet, fluid_id(ids, n), R(sx * il), R(sy * il), R(sz * il), R(cos(th)));
 }
 
 // Dense copy (4 reals per node, node-major) of the per-fluid-id wetting data; zero at solids.
 template <class R>
-__global__ void k_wet_dense(int N, const int* fid, const R* wet, R* out) {
+__global__ void k_wet_dense(int N, const uint32_t* info, const IdWord* ids, const R* wet, R* out) {
   const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
-  const int f = fid[n];
-  if (f >= 0) {
-    const typename V4<R>::T v = ld4(wet, f);
-    st4(out, n, v.x, v.y, v.z, v.w);
+  if (info[n] & kFluid) {
+    const typename V4<R>::T v = ld4<size_t>(wet, fluid_id(ids, n));
+    st4<size_t>(out, n, v.x, v.y, v.z, v.w);
   } else {
-    st4(out, n, R(0), R(0), R(0), R(0));
+    st4<size_t>(out, n, R(0), R(0), R(0), R(0));
   }
 }
 
@@ -355,15 +365,15 @@ __global__ void k_init_state(StepArgs<P> A, const double* rr0, const double* rp0
   using D = D3Q19;
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= A.nfluid) return;
-  const int n = A.fluid[t];
+  const int n = A.fluid[t].node;
   const double rm = rr0[n] + rp0[n];
   for (int i = 0; i < 19; ++i) A.fout[size_t(i) * A.ps + t] = Prec<P>::st(R(D::w(i) * rm), R(D::w(i)), A.scale);
-  st4(A.aout, t, R(pack_frac(rr0[n] / rm, rp0[n] / rm)), R(0), R(0), R(0));
+  st4<size_t>(A.aout, t, R(pack_frac(rr0[n] / rm, rp0[n] / rm)), R(0), R(0), R(0));
   if (A.species) {
     const double c = c0 ? c0[n] : 1.0;
-    if (P >= 2) A.cout[t] = R(c);  // deviations from w_q C: zero at rest
+    if (Prec<P>::deviations) A.cout[t] = R(c);  // deviations from w_q C: zero at rest
     for (int i = 0; i < 7; ++i)
-      A.gout[size_t(i) * A.ps + t] = Prec<P>::st(R(D3Q7::w(i) * c), P >= 2 ? R(D3Q7::w(i)) * R(c) : R(D3Q7::w(i)), A.gscale);
+      A.gout[size_t(i) * A.ps + t] = Prec<P>::st(R(D3Q7::w(i) * c), Prec<P>::deviations ? R(D3Q7::w(i)) * R(c) : R(D3Q7::w(i)), A.gscale);
   }
 }
 
@@ -376,21 +386,9 @@ __global__ void k_flag_count(const uint32_t* info, int N, uint32_t mask, int* co
 }
 
 // First node of each tile of kBlock consecutive fluid ids.
-__global__ void k_tile_heads(const int* fluid, int ntiles, int* heads) {
+__global__ void k_tile_heads(const ListNode* fluid, int ntiles, int* heads) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < ntiles) heads[k] = fluid[size_t(k) * kBlock];
-}
-
-__global__ void k_gather_info(const uint32_t* info, const int* list, int len, uint32_t* out) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < len) out[t] = info[list[t]];
-}
-
-// Fluid id of every node (-1 for solid): the inverse of the fluid list.
-__global__ void k_fill_fid(const uint32_t* info, const int* list, int N, int nfluid, int* fid) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n < N && !(info[n] & kFluid)) fid[n] = -1;
-  if (n < nfluid) fid[list[n]] = n;
+  if (k < ntiles) heads[k] = fluid[size_t(k) * kBlock].node;
 }
 
 __global__ void k_scan_counts(int* counts, int nb) {
@@ -411,7 +409,9 @@ __global__ void k_scan_counts(int* counts, int nb) {
   for (int b = b0; b < b1; ++b) { const int v = counts[b]; counts[b] = run; run += v; }
 }
 
-__global__ void k_flag_scatter(const uint32_t* info, int N, uint32_t mask, const int* offsets, int* list) {
+// ids (may be null): the id map of the flagged nodes.
+__global__ void k_flag_scatter(const uint32_t* info, int N, uint32_t mask, const int* offsets, Geom g, ListNode* list,
+                               IdWord* ids) {
   __shared__ int wsum[4];
   const int n = blockIdx.x * blockDim.x + threadIdx.x;
   const bool f = n < N && (info[n] & mask);
@@ -423,7 +423,13 @@ __global__ void k_flag_scatter(const uint32_t* info, int N, uint32_t mask, const
   __syncthreads();
   int off = offsets[blockIdx.x];
   for (int w = 0; w < wave; ++w) off += wsum[w];
-  if (f) list[off + pre] = n;
+  if (f) {
+    const int row = int(g.fx.div(uint32_t(n))), x = n - row * g.nx, z = int(g.fy.div(uint32_t(row))), y = row - z * g.ny;
+    const uint32_t faces = uint32_t(x == 0) | uint32_t(x == g.nx - 1) << 1 | uint32_t(y == 0) << 2 |
+                           uint32_t(y == g.ny - 1) << 3 | uint32_t(z == 0) << 4 | uint32_t(z == g.nz - 1) << 5;
+    list[off + pre] = {n, info[n] | faces << kFaceShift};
+  }
+  if (ids && n < N && lane % 32 == 0) ids[n / 32] = {uint32_t(bal >> (lane & 32)), uint32_t(off + pre)};
 }
 
 FastDiv make_fastdiv(uint32_t d) {
@@ -434,6 +440,14 @@ FastDiv make_fastdiv(uint32_t d) {
   f.s = s;
   f.m = uint32_t(((uint64_t(1) << 32) * ((uint64_t(1) << s) - d)) / d + 1);
   return f;
+}
+
+Geom make_geom(const lbm_params& p) {
+  Geom g;
+  g.nx = p.nx; g.ny = p.ny; g.nz = p.nz;
+  g.fx = make_fastdiv(uint32_t(p.nx));
+  g.fy = make_fastdiv(uint32_t(p.ny));
+  return g;
 }
 
 int rounded_blocks(int n) {
@@ -455,15 +469,11 @@ StepArgs<P> make_args(lbm_ctx* c, int src_buf) {
   const Layout& L = c->L;
   A.nx = p.nx; A.ny = p.ny; A.nz = p.nz; A.N = c->N;
   A.ps = L.ps;
-  A.geo.nx = p.nx; A.geo.ny = p.ny; A.geo.nz = p.nz;
-  A.geo.fx = make_fastdiv(uint32_t(p.nx));
-  A.geo.fy = make_fastdiv(uint32_t(p.ny));
-  A.fluid = reinterpret_cast<const int*>(c->ws + L.lists[0]);
-  A.finfo = reinterpret_cast<const uint32_t*>(c->ws + L.linfo[0]);
+  A.geo = make_geom(p);
+  A.fluid = reinterpret_cast<const ListNode*>(c->ws + L.lists[0]);
   A.nfluid = c->nfluid;
-  A.ext = reinterpret_cast<const int*>(c->ws + L.lists[1]);
-  A.einfo = reinterpret_cast<const uint32_t*>(c->ws + L.linfo[1]);
-  A.fid = reinterpret_cast<const int*>(c->ws + L.fid);
+  A.ext = reinterpret_cast<const ListNode*>(c->ws + L.lists[1]);
+  A.ids = reinterpret_cast<const IdWord*>(c->ws + L.ids);
   A.order = c->ordered ? reinterpret_cast<const int*>(c->ws + L.order) : nullptr;
   A.next = c->next;
   A.info = reinterpret_cast<const uint32_t*>(c->ws + L.info);
@@ -527,7 +537,7 @@ lbm_status enqueue_step(lbm_ctx* c, const StepArgs<P>& A, hipEvent_t* ev, bool c
 }
 
 template <int P>
-lbm_status launch_step(lbm_ctx* c, int slot, bool timed = true, void* fields = nullptr) {
+lbm_status launch_step(lbm_ctx* c, int slot, bool timed, void* fields) {
   StepArgs<P> A = make_args<P>(c, c->cur);
   if (fields) use_fields<P>(c, A, fields);
   double* ring = reinterpret_cast<double*>(c->ws + c->L.ring);
@@ -635,7 +645,7 @@ lbm_status build_tile_order(lbm_ctx* c) {
   if (3.0 * double(c->nfluid) / nz * node_bytes <= kOrderBytes) return LBM_OK;
   int* d_order = reinterpret_cast<int*>(c->ws + c->L.order);
   hipLaunchKernelGGL(k_tile_heads, dim3((ntiles + kBlock - 1) / kBlock), dim3(kBlock), 0, c->stream,
-                     reinterpret_cast<const int*>(c->ws + c->L.lists[0]), ntiles, d_order);
+                     reinterpret_cast<const ListNode*>(c->ws + c->L.lists[0]), ntiles, d_order);
   HIP_TRY(c, hipGetLastError());
   std::vector<int> heads(ntiles);
   HIP_TRY(c, hipMemcpyAsync(heads.data(), d_order, sizeof(int) * size_t(ntiles), hipMemcpyDeviceToHost, c->stream));
@@ -664,31 +674,26 @@ lbm_status launch_init(lbm_ctx* c, const uint8_t* d_solid, const uint8_t* d_reac
   uint32_t* info = reinterpret_cast<uint32_t*>(c->ws + c->L.info);
   hipLaunchKernelGGL(k_init_info, dim3(gb), dim3(tb), 0, c->stream, p.nx, p.ny, p.nz, d_solid, d_react,
                      int(p.species && p.x_open), info);
+  IdWord* ids = reinterpret_cast<IdWord*>(c->ws + c->L.ids);
+  const Geom geo = make_geom(p);
   // Launch lists: fluid nodes and solid nodes with extrapolated colour, in node order.
   int* counts = reinterpret_cast<int*>(c->ws + c->L.counts);
   const uint32_t masks[2] = {kFluid, kExtrap};
   int lens[2] = {0, 0};
   for (int k = 0; k < 2; ++k) {
-    int* list = reinterpret_cast<int*>(c->ws + c->L.lists[k]);
+    ListNode* list = reinterpret_cast<ListNode*>(c->ws + c->L.lists[k]);
     hipLaunchKernelGGL(k_flag_count, dim3(gb), dim3(tb), 0, c->stream, info, c->N, masks[k], counts);
     hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, c->stream, counts, gb);
-    hipLaunchKernelGGL(k_flag_scatter, dim3(gb), dim3(tb), 0, c->stream, info, c->N, masks[k], counts, list);
+    hipLaunchKernelGGL(k_flag_scatter, dim3(gb), dim3(tb), 0, c->stream, info, c->N, masks[k], counts, geo, list,
+                       k == 0 ? ids : nullptr);
     HIP_TRY(c, hipMemcpyAsync(&lens[k], counts + gb, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   c->nfluid = lens[0];
   c->next = lens[1];
-  hipLaunchKernelGGL(k_fill_fid, dim3(gb), dim3(tb), 0, c->stream, info,
-                     reinterpret_cast<const int*>(c->ws + c->L.lists[0]), c->N, c->nfluid,
-                     reinterpret_cast<int*>(c->ws + c->L.fid));
   hipLaunchKernelGGL(k_init_wet<R>, dim3(gb), dim3(tb), 0, c->stream, p.nx, p.ny, p.nz, d_solid, info,
-                     reinterpret_cast<const int*>(c->ws + c->L.fid), d_theta, theta_uniform,
+                     ids, d_theta, theta_uniform,
                      reinterpret_cast<R*>(c->ws + c->L.wet));
-  for (int k = 0; k < 2; ++k)
-    if (lens[k] > 0)
-      hipLaunchKernelGGL(k_gather_info, dim3((lens[k] + tb - 1) / tb), dim3(tb), 0, c->stream, info,
-                         reinterpret_cast<const int*>(c->ws + c->L.lists[k]), lens[k],
-                         reinterpret_cast<uint32_t*>(c->ws + c->L.linfo[k]));
   c->nb_fluid = rounded_blocks(c->nfluid);
   c->nb_ext = rounded_blocks(c->next);
   if (lbm_status s = build_tile_order(c); s != LBM_OK) return s;
@@ -807,13 +812,25 @@ lbm_status check_adjoint_buffers(lbm_ctx* c, const void* state, const void* fiel
   return LBM_OK;
 }
 
-#define DISPATCH(ctx, fn, ...)                                   \
-  switch ((ctx)->p.precision) {                                  \
-    case LBM_FP64: return fn<0>((ctx), __VA_ARGS__);             \
-    case LBM_FP32: return fn<1>((ctx), __VA_ARGS__);             \
-    case LBM_FP16_DEV: return fn<2>((ctx), __VA_ARGS__);         \
-    default: return fn<3>((ctx), __VA_ARGS__);                   \
+// fn<mode>(ctx, ...) for the context's mode.
+#define DISPATCH(ctx, fn, ...)                                                  \
+  switch ((ctx)->mode) {                                                        \
+    case LBM_FP64: return fn<LBM_FP64>((ctx), __VA_ARGS__);                     \
+    case LBM_FP32: return fn<LBM_FP32>((ctx), __VA_ARGS__);                     \
+    case LBM_FP16_DEV: return fn<LBM_FP16_DEV>((ctx), __VA_ARGS__);             \
+    case LBM_BF16_DEV: return fn<LBM_BF16_DEV>((ctx), __VA_ARGS__);             \
+    case kWideMode + LBM_FP64: return fn<kWideMode + LBM_FP64>((ctx), __VA_ARGS__);         \
+    case kWideMode + LBM_FP32: return fn<kWideMode + LBM_FP32>((ctx), __VA_ARGS__);         \
+    case kWideMode + LBM_FP16_DEV: return fn<kWideMode + LBM_FP16_DEV>((ctx), __VA_ARGS__); \
+    default: return fn<kWideMode + LBM_BF16_DEV>((ctx), __VA_ARGS__);           \
   }
+
+lbm_status step_once(lbm_ctx* c, int slot, bool timed, void* fields) { DISPATCH(c, launch_step, slot, timed, fields); }
+lbm_status init_once(lbm_ctx* c, const uint8_t* solid, const uint8_t* react, const double* theta, double theta_uniform,
+                     const double* rr, const double* rp, const double* c0) {
+  DISPATCH(c, launch_init, solid, react, theta, theta_uniform, rr, rp, c0);
+}
+lbm_status state_sums_once(lbm_ctx* c, const void* state, double* out) { DISPATCH(c, launch_state_sums, state, out); }
 
 }  // namespace
 
@@ -888,6 +905,7 @@ lbm_status lbm_init(const lbm_params* params, const uint8_t* solid, const double
   lbm_ctx* c = new (std::nothrow) lbm_ctx();
   if (!c) return LBM_ERR_ALLOC;
   c->p = *params;
+  c->mode = params->precision + (use_wide_offsets(*params) ? kWideMode : 0);
   c->N = int(N);
   c->L = L;
   c->ws = static_cast<char*>(d_workspace);
@@ -929,13 +947,8 @@ lbm_status lbm_init(const lbm_params* params, const uint8_t* solid, const double
   INIT_TRY(hipMemcpyAsync(d_rr, rho_r0, 8 * N, hipMemcpyHostToDevice, c->stream));
   INIT_TRY(hipMemcpyAsync(d_rp, rho_p0, 8 * N, hipMemcpyHostToDevice, c->stream));
   if (c0) INIT_TRY(hipMemcpyAsync(d_c0, c0, 8 * N, hipMemcpyHostToDevice, c->stream));
-  lbm_status st;
-  switch (c->p.precision) {
-    case LBM_FP64: st = launch_init<0>(c, d_solid, reactive ? d_react : nullptr, theta ? d_theta : nullptr, theta_uniform, d_rr, d_rp, c0 ? d_c0 : nullptr); break;
-    case LBM_FP32: st = launch_init<1>(c, d_solid, reactive ? d_react : nullptr, theta ? d_theta : nullptr, theta_uniform, d_rr, d_rp, c0 ? d_c0 : nullptr); break;
-    case LBM_FP16_DEV: st = launch_init<2>(c, d_solid, reactive ? d_react : nullptr, theta ? d_theta : nullptr, theta_uniform, d_rr, d_rp, c0 ? d_c0 : nullptr); break;
-    default: st = launch_init<3>(c, d_solid, reactive ? d_react : nullptr, theta ? d_theta : nullptr, theta_uniform, d_rr, d_rp, c0 ? d_c0 : nullptr); break;
-  }
+  const lbm_status st = init_once(c, d_solid, reactive ? d_react : nullptr, theta ? d_theta : nullptr, theta_uniform, d_rr,
+                                  d_rp, c0 ? d_c0 : nullptr);
   if (st != LBM_OK) return bail(st);
   // The host inputs are pageable memory; finish the copies before returning to the caller.
   INIT_TRY(hipStreamSynchronize(c->stream));
@@ -953,14 +966,7 @@ lbm_status lbm_step(lbm_ctx* c, int32_t nsteps, lbm_reductions* per_step) {
   while (done < nsteps) {
     const int chunk = std::min(kRing, nsteps - done);
     for (int t = 0; t < chunk; ++t) {
-      lbm_status s;
-      switch (c->p.precision) {
-        case LBM_FP64: s = launch_step<0>(c, t); break;
-        case LBM_FP32: s = launch_step<1>(c, t); break;
-        case LBM_FP16_DEV: s = launch_step<2>(c, t); break;
-        default: s = launch_step<3>(c, t); break;
-      }
-      if (s != LBM_OK) return s;
+      if (lbm_status s = step_once(c, t, true, nullptr); s != LBM_OK) return s;
     }
     if (lbm_status s = launch_finish(c, chunk - 1); s != LBM_OK) return s;
     rows.resize(5 * size_t(chunk));
@@ -997,15 +1003,7 @@ lbm_status lbm_step_async(lbm_ctx* c, int32_t nsteps) {
   if (!c) return LBM_ERR_ARG;
   if (nsteps < 0) return fail(c, LBM_ERR_ARG, "nsteps must be >= 0");
   for (int t = 0; t < nsteps; ++t) {
-    lbm_status s;
-    const int slot = t % kRing;
-    switch (c->p.precision) {
-      case LBM_FP64: s = launch_step<0>(c, slot, false); break;
-      case LBM_FP32: s = launch_step<1>(c, slot, false); break;
-      case LBM_FP16_DEV: s = launch_step<2>(c, slot, false); break;
-      default: s = launch_step<3>(c, slot, false); break;
-    }
-    if (s != LBM_OK) return s;
+    if (lbm_status s = step_once(c, t % kRing, false, nullptr); s != LBM_OK) return s;
   }
   return LBM_OK;
 }
@@ -1020,12 +1018,7 @@ lbm_status lbm_fields_bytes(const lbm_params* params, size_t* bytes) {
 lbm_status lbm_step_fields(lbm_ctx* c, void* d_fields) {
   if (!c) return LBM_ERR_ARG;
   if (!d_fields) return fail(c, LBM_ERR_ARG, "a fields buffer is required");
-  switch (c->p.precision) {
-    case LBM_FP64: return launch_step<0>(c, 0, false, d_fields);
-    case LBM_FP32: return launch_step<1>(c, 0, false, d_fields);
-    case LBM_FP16_DEV: return launch_step<2>(c, 0, false, d_fields);
-    default: return launch_step<3>(c, 0, false, d_fields);
-  }
+  return step_once(c, 0, false, d_fields);
 }
 
 lbm_status lbm_step_from(lbm_ctx* c, const void* d_src, void* d_dst, void* d_fields) {
@@ -1051,14 +1044,7 @@ lbm_status lbm_state_sums(lbm_ctx* c, const void* d_state, lbm_reductions* out) 
   if (!c) return LBM_ERR_ARG;
   if (!out) return fail(c, LBM_ERR_ARG, "out is NULL");
   double row[5] = {0, 0, 0, 0, 0};
-  lbm_status s;
-  switch (c->p.precision) {
-    case LBM_FP64: s = launch_state_sums<0>(c, d_state, row); break;
-    case LBM_FP32: s = launch_state_sums<1>(c, d_state, row); break;
-    case LBM_FP16_DEV: s = launch_state_sums<2>(c, d_state, row); break;
-    default: s = launch_state_sums<3>(c, d_state, row); break;
-  }
-  if (s != LBM_OK) return s;
+  if (lbm_status s = state_sums_once(c, d_state, row); s != LBM_OK) return s;
   out->mass_r = row[0];
   out->mass_p = row[1];
   out->conversion = 0.0;
@@ -1079,12 +1065,13 @@ lbm_status lbm_geometry(lbm_ctx* c, void* d_info, void* d_wet) {
   if (d_info) HIP_TRY(c, hipMemcpyAsync(d_info, c->ws + c->L.info, 4 * N, hipMemcpyDeviceToDevice, c->stream));
   if (d_wet) {
     const int tb = 256, gb = int((N + tb - 1) / tb);
-    const int* fid = reinterpret_cast<const int*>(c->ws + c->L.fid);
+    const IdWord* ids = reinterpret_cast<const IdWord*>(c->ws + c->L.ids);
+    const uint32_t* info = reinterpret_cast<const uint32_t*>(c->ws + c->L.info);
     if (c->p.precision == LBM_FP64)
-      hipLaunchKernelGGL(k_wet_dense<double>, dim3(gb), dim3(tb), 0, c->stream, int(N), fid,
+      hipLaunchKernelGGL(k_wet_dense<double>, dim3(gb), dim3(tb), 0, c->stream, int(N), info, ids,
                          reinterpret_cast<const double*>(c->ws + c->L.wet), static_cast<double*>(d_wet));
     else
-      hipLaunchKernelGGL(k_wet_dense<float>, dim3(gb), dim3(tb), 0, c->stream, int(N), fid,
+      hipLaunchKernelGGL(k_wet_dense<float>, dim3(gb), dim3(tb), 0, c->stream, int(N), info, ids,
                          reinterpret_cast<const float*>(c->ws + c->L.wet), static_cast<float*>(d_wet));
     HIP_TRY(c, hipGetLastError());
   }

@@ -3,8 +3,8 @@
 // Storage. The state arrays hold fluid nodes only, indexed by fluid id (the rank of the node
 // among fluid nodes in node order, so rows stay contiguous); thread t of a launch is fluid node t
 // and writes its own slot, which makes every store a full coalesced line. Pulls find the id of
-// the source node through a dense node -> id map. The small per-node fields (rho^N, the info
-// word, the id map) stay dense, because the stencils also read them at solid nodes.
+// the source node through a map of fluid bits and counts (IdWord). The small per-node fields
+// (rho^N, the info word) stay dense, because the stencils also read them at solid nodes.
 //
 // State representation. Under Latva-Kokko recolouring of the colour-blind post-collision
 // populations (eq. operator_recoloring) followed by the proportional wall-reaction transfer,
@@ -48,8 +48,7 @@
 namespace lbm {
 
 constexpr int kBlock = 256;
-constexpr int kXcd = 8;
-
+constexpr int kXcd = 8;  // MI355X: 8 XCDs; workgroups are dealt round-robin across them
 
 // Per-node 4-vectors (colour scalars a, v; realigned normal and |G|; wetting data) are stored
 // together (16 or 32 bytes per node) so that one load brings all four: a gather's cost follows
@@ -60,14 +59,45 @@ template <> struct V4<double> { using T = double4; };
 template <class R> struct V2;
 template <> struct V2<float> { using T = float2; };
 template <> struct V2<double> { using T = double2; };
-template <class R>
-__device__ inline typename V4<R>::T ld4(const R* p, size_t n) { return reinterpret_cast<const typename V4<R>::T*>(p)[n]; }
-template <class R>
-__device__ inline void st4(R* p, size_t n, R x, R y, R z, R w) {
+
+// Element i of an array: with a 32-bit index type as a 32-bit byte offset from the (wave-uniform)
+// base, which the caller knows to suffice; else with a 64-bit address.
+template <class Off, class T>
+__device__ inline T ldx(const T* base, Off i) {
+  if constexpr (sizeof(Off) == 4)
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + uint32_t(i * uint32_t(sizeof(T))));
+  else
+    return base[i];
+}
+template <class Off, class T>
+__device__ inline T& refx(T* base, Off i) {
+  if constexpr (sizeof(Off) == 4)
+    return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + uint32_t(i * uint32_t(sizeof(T))));
+  else
+    return base[i];
+}
+template <class Off, class R>
+__device__ inline typename V4<R>::T ld4(const R* p, Off n) {
+  return ldx<Off>(reinterpret_cast<const typename V4<R>::T*>(p), n);
+}
+template <class Off, class R>
+__device__ inline void st4(R* p, Off n, R x, R y, R z, R w) {
   typename V4<R>::T v;
   v.x = x; v.y = y; v.z = z; v.w = w;
-  reinterpret_cast<typename V4<R>::T*>(p)[n] = v;
-}  // MI355X: 8 XCDs; workgroups are dealt round-robin across them
+  refx<Off>(reinterpret_cast<typename V4<R>::T*>(p), n) = v;
+}
+
+// Uses all four components of a loaded vector. A load of which only some components are used is
+// otherwise split, and a gather costs by the instruction and its cache lines, not by the words.
+__device__ inline void use_whole(const float4& v) { asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w)); }
+__device__ inline void use_whole(const double4& v) { asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w)); }
+
+// a b rounded, never fused into a following sum.
+template <class R>
+__device__ inline R rounded_product(R a, R b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
 
 // A pair of colour fractions (a, b), a + b = 1, stored as one number that holds the smaller one
 // to full relative precision: e = -|b| (sign bit set) when 0 <= b <= a or a < 0, else e = |a|.
@@ -80,13 +110,9 @@ __device__ inline R pack_frac(R a, R b) {
 }
 template <class R>
 __device__ inline void unpack_frac(R e, R& a, R& b) {
-  if (signbit(e)) {
-    b = -e;
-    a = R(1) - b;
-  } else {
-    a = e;
-    b = R(1) - a;
-  }
+  const R minor = fabs(e), major = R(1) - minor;
+  a = signbit(e) ? major : minor;
+  b = signbit(e) ? minor : major;
 }
 // rho^N = a - b is stored as q = rho^N - s with s = +1 if the sign bit of q is set (product
 // colour in the minority, q = -2b) and s = -1 otherwise (q = 2a).
@@ -130,16 +156,6 @@ __device__ inline int fluid_tile(const SA& A) {
   return A.order ? A.order[lb] : lb;
 }
 
-// Periodic neighbour offsets of one node.
-struct Nbr {
-  int n, x;
-  int dxm, dxp, dym, dyp, dzm, dzp;
-  __device__ inline int at(int cx, int cy, int cz) const {
-    return n + (cx > 0 ? dxp : (cx < 0 ? dxm : 0)) + (cy > 0 ? dyp : (cy < 0 ? dym : 0)) +
-           (cz > 0 ? dzp : (cz < 0 ? dzm : 0));
-  }
-};
-
 // Division by a runtime constant d for 0 <= n < 2^31: q = (umulhi(n, m) + n) >> s with
 // s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1 (computed on the host).
 struct FastDiv {
@@ -152,21 +168,66 @@ struct Geom {
   FastDiv fx, fy;
 };
 
-__device__ inline Nbr make_nbr(int n, const Geom& g) {
+// All ones where bit i of w is set, else zero, and selects by such masks. The masks stay in vector
+// registers and each select is one v_bfi: a lane mask in scalar registers costs a compare per use
+// (18 link bits do not stay resident) and two wait states between the compare and the select. The
+// instruction is written out because the compiler turns the builtin back into compare and select.
+__device__ inline uint32_t bit_mask(uint32_t w, int i) {
+  uint32_t m = 0u - ((w >> i) & 1u);
+  if (__builtin_constant_p(i)) asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(w), "n"(i));
+  return m;
+}
+__device__ inline uint32_t blend(uint32_t m, uint32_t a, uint32_t b) { return (m & a) | (~m & b); }
+__device__ inline float blend(uint32_t m, float a, float b) {
+  return __uint_as_float(blend(m, __float_as_uint(a), __float_as_uint(b)));
+}
+__device__ inline double blend(uint32_t m, double a, double b) {
+  const uint64_t x = uint64_t(__double_as_longlong(a)), y = uint64_t(__double_as_longlong(b));
+  return __longlong_as_double((long long)((uint64_t(blend(m, uint32_t(x >> 32), uint32_t(y >> 32))) << 32) |
+                                          blend(m, uint32_t(x), uint32_t(y))));
+}
+__device__ inline float2 blend(uint32_t m, const float2& a, const float2& b) {
+  return make_float2(blend(m, a.x, b.x), blend(m, a.y, b.y));
+}
+__device__ inline double2 blend(uint32_t m, const double2& a, const double2& b) {
+  return make_double2(blend(m, a.x, b.x), blend(m, a.y, b.y));
+}
+__device__ inline float4 blend(uint32_t m, const float4& a, const float4& b) {
+  return make_float4(blend(m, a.x, b.x), blend(m, a.y, b.y), blend(m, a.z, b.z), blend(m, a.w, b.w));
+}
+__device__ inline double4 blend(uint32_t m, const double4& a, const double4& b) {
+  return make_double4(blend(m, a.x, b.x), blend(m, a.y, b.y), blend(m, a.z, b.z), blend(m, a.w, b.w));
+}
+
+// Entry of a launch list.
+struct ListNode {
+  int node;
+  uint32_t info;  // its info word, with the face bits
+};
+
+// Periodic neighbour offsets of one node.
+struct Nbr {
+  int n;
+  int dxm, dxp, dym, dyp, dzm, dzp;
+  __device__ inline int at(int cx, int cy, int cz) const {
+    return n + (cx > 0 ? dxp : (cx < 0 ? dxm : 0)) + (cy > 0 ? dyp : (cy < 0 ? dym : 0)) +
+           (cz > 0 ? dzp : (cz < 0 ? dzm : 0));
+  }
+};
+
+// From the face bits: the division of n by the lattice sizes takes five products at a quarter of the
+// rate, a tenth of the colour pass's instruction time.
+__device__ inline Nbr make_nbr(int n, uint32_t inf, const Geom& g) {
+  const int nx = g.nx, nxy = g.nx * g.ny, N = nxy * g.nz;
+  auto face = [&](int k) { return int(bit_mask(inf, kFaceShift + k)); };
   Nbr b;
   b.n = n;
-  const uint32_t t = g.fx.div(uint32_t(n));
-  const int x = n - int(t) * g.nx;
-  const int z = int(g.fy.div(t));
-  const int y = int(t) - z * g.ny;
-  const int nx = g.nx, ny = g.ny, nz = g.nz, nxy = nx * ny;
-  b.x = x;
-  b.dxm = (x == 0) ? nx - 1 : -1;
-  b.dxp = (x == nx - 1) ? -(nx - 1) : 1;
-  b.dym = (y == 0) ? (ny - 1) * nx : -nx;
-  b.dyp = (y == ny - 1) ? -(ny - 1) * nx : nx;
-  b.dzm = (z == 0) ? (nz - 1) * nxy : -nxy;
-  b.dzp = (z == nz - 1) ? -(nz - 1) * nxy : nxy;
+  b.dxm = (face(0) & nx) - 1;
+  b.dxp = 1 - (face(1) & nx);
+  b.dym = (face(2) & nxy) - nx;
+  b.dyp = nx - (face(3) & nxy);
+  b.dzm = (face(4) & N) - nxy;
+  b.dzp = nxy - (face(5) & N);
   return b;
 }
 
@@ -178,68 +239,71 @@ constexpr int yz_partner(int i) {
   return -1;
 }
 
+// Map from nodes to fluid ids. Word w covers the nodes n = 32 w .. 32 w + 31: the bits of the fluid
+// ones, and the number of fluid nodes before the first of them in dense order. The number of fluid
+// nodes before any node, fluid or solid, is then a bit count away, and at a fluid node that is its
+// id. Against a dense map (4 bytes per node) it takes a sixteenth of the bytes, and the lookups of a
+// wave, whose nodes span about 64 / porosity of a row, touch one or two cache lines per row instead
+// of four. Measured with the dense map: 512 x 512 x 128 porous, FP32, colour 604 -> 580 us and
+// collide 1123 -> 1084 us; at 128^3, which stays in the last-level cache, the same time.
+struct IdWord {
+  uint32_t fluid, before;
+};
+__device__ inline uint32_t fluid_before(IdWord w, uint32_t n) { return __popc(w.fluid & ((1u << (n & 31u)) - 1u)) + w.before; }
+__device__ inline uint32_t fluid_id(const IdWord* ids, int n) { return fluid_before(ids[n >> 5], uint32_t(n)); }
+
 // Fluid ids of the 18 pull sources x - c_i of fluid node t, the node's own id where the source is
-// solid. Fluid ids are ranks in dense order, so two fluid nodes next to each other along x within
-// a row (no periodic wrap) have ids one apart: a source x - c_i with c_ix != 0 takes the id of its
-// partner (x, y - c_iy, z - c_iz) minus c_ix when the partner is fluid, and the id map is read only
-// for the other sources. All of those reads are issued before any id is formed, so they are in
-// flight together.
-// x - cx (cx = +-1) is the next node along the row of x (no periodic wrap between them).
-__device__ inline bool row_step(const Nbr& nb, int cx) { return cx > 0 ? nb.dxm == -1 : nb.dxp == 1; }
-
-__device__ inline void pull_sources(const int* fid, const Nbr& nb, int t, uint32_t inf, int sid[18]) {
+// solid. With the count r of fluid nodes before the row centre x - (0, c_iy, c_iz), a fluid source
+// one node before it on the row has id r - 1 and one after it r + 1 (r where the centre is solid),
+// so eight lookups give all 18 ids; only a lane at a periodic x face looks up the five sources
+// across the face. All lookups are issued before any id is formed.
+template <class Off>
+__device__ inline void pull_sources(const IdWord* ids, const Nbr& nb, uint32_t t, uint32_t inf, uint32_t sid[18]) {
   using D = D3Q19;
-  // Which ids follow from a neighbour's: known from the info bits alone, before any load.
-  bool derived[18];
-#pragma unroll
-  for (int i = 0; i < 18; ++i) {
-    const int m = yz_partner(i);
-    const bool mfluid = (m < 0) || !((inf >> m) & 1u);
-    derived[i] = (D::cx[i] != 0) && mfluid && row_step(nb, D::cx[i]);
-  }
-  // Every id-map read first, so that they are in flight together; only then the ids.
-  int look[18];
-#pragma unroll
-  for (int i = 0; i < 18; ++i) {
-    look[i] = 0;
-    if (!((inf >> i) & 1u) && !derived[i]) look[i] = fid[nb.at(-D::cx[i], -D::cy[i], -D::cz[i])];
-  }
+  uint32_t centre[18];
+  IdWord w[18];
 #pragma unroll
   for (int i = 0; i < 18; ++i)
-    if (D::cx[i] == 0) sid[i] = ((inf >> i) & 1u) ? t : look[i];
+    if (D::cx[i] == 0) {
+      centre[i] = uint32_t(nb.at(0, -D::cy[i], -D::cz[i]));
+      w[i] = ldx<Off>(ids, centre[i] >> 5);
+    }
+  const uint32_t low = bit_mask(inf, kFaceShift), high = bit_mask(inf, kFaceShift + 1);
+  // the source across the x face on the node's own row (1) and the rows of directions 2..5
+  IdWord aw[6];
+  const uint32_t dx = uint32_t(blend(low, uint32_t(nb.dxm), uint32_t(nb.dxp)));  // a row of one node has both, the same node
+  centre[1] = uint32_t(nb.n);
+  if (low | high) {
 #pragma unroll
-  for (int i = 0; i < 18; ++i) {
-    if (D::cx[i] == 0) continue;
-    const int m = yz_partner(i);
-    const int mid = (m < 0) ? t : sid[m];
-    sid[i] = ((inf >> i) & 1u) ? t : (derived[i] ? mid - D::cx[i] : look[i]);
+    for (int i = 1; i < 6; ++i) aw[i] = ldx<Off>(ids, (centre[i] + dx) >> 5);
   }
-}
-
-// The same ids with fewer registers live: each id-map read is consumed as it arrives, so the reads
-// are not all in flight at once. For the adjoint passes, whose other state leaves few registers
-// (the batched form made them spill or lose a wave per SIMD).
-__device__ inline void pull_sources_lean(const int* fid, const Nbr& nb, int t, uint32_t inf, int sid[18]) {
-  using D = D3Q19;
+  uint32_t r[18], across[6];
+#pragma unroll
+  for (int i = 1; i < 6; ++i) across[i] = fluid_before(aw[i], centre[i] + dx);
 #pragma unroll
   for (int i = 0; i < 18; ++i)
-    if (D::cx[i] == 0) sid[i] = ((inf >> i) & 1u) ? t : fid[nb.at(0, -D::cy[i], -D::cz[i])];
+    if (D::cx[i] == 0) r[i] = fluid_before(w[i], centre[i]);
 #pragma unroll
   for (int i = 0; i < 18; ++i) {
-    if (D::cx[i] == 0) continue;
     const int m = yz_partner(i);
-    const int mid = (m < 0) ? t : sid[m];
-    const bool mfluid = (m < 0) || !((inf >> m) & 1u);
-    sid[i] = ((inf >> i) & 1u) ? t : ((mfluid && row_step(nb, D::cx[i])) ? mid - D::cx[i] : fid[nb.at(-D::cx[i], -D::cy[i], -D::cz[i])]);
+    uint32_t id;
+    if (D::cx[i] == 0) {
+      id = r[i];
+    } else if (D::cx[i] > 0) {
+      id = blend(low, across[m < 0 ? 1 : m], (m < 0 ? t : r[m]) - 1u);
+    } else {
+      id = blend(high, across[m < 0 ? 1 : m], m < 0 ? t + 1u : r[m] + 1u + bit_mask(inf, m));
+    }
+    sid[i] = blend(bit_mask(inf, i), t, id);
   }
 }
 
 // Cross-lane moves within the 64-wide wave (DPP wave shifts, one VALU move per 32-bit word): the
 // value that lane l - 1 (from_below) or lane l + 1 (from_above) holds in the same register. The end
-// lanes of the wave receive their own value; callers use the result only where the neighbouring
-// lane is active and holds the wanted node.
-__device__ inline int lane_from_below(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x138, 0xf, 0xf, false); }
-__device__ inline int lane_from_above(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x130, 0xf, 0xf, false); }
+// lanes of the wave receive zero; callers use the result only where the neighbouring lane is
+// active and holds the wanted node.
+__device__ inline int lane_from_below(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
+__device__ inline int lane_from_above(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
 template <int DIR>
 __device__ inline float lane_move(float v) {
   const int b = __float_as_int(v);
@@ -275,56 +339,99 @@ __device__ inline double4 lane_move(const double4& v) {
 // x - (0, c_iy, c_iz) of the partner direction, one node along x; when the node's own neighbour
 // x - c_ix along the row is fluid, it is the next fluid id and lane l - c_ix of the same wave holds
 // it, and that lane's partner value is exactly the one wanted. Those values are moved across lanes
-// instead of gathered, so each row triple costs one gather; the other lanes (wave ends, periodic
-// wrap, a solid neighbour along x) gather their own. ld(i) gathers the value of direction i; own is
-// the node's own value (the source of the x-shifted directions of the node's own row). SOLID_OWN:
-// where x - c_i is solid the node's own value stands in (state vectors, whose solid sources are
-// bounce-back); otherwise every neighbour has a value of its own (rho^N, extrapolated into solids).
+// instead of gathered, so each row triple costs one gather for all lanes. The lanes that cannot be
+// served so (wave ends, periodic wrap, a solid neighbour along x) lack one of the row's two shifted
+// sources: the first node of a run of fluid nodes the one before it, the last node the one after it.
+// Both kinds share one masked gather per row, each lane with the index of the source it lacks; the
+// few lanes that lack both (runs of a single node; 6% of the waves of the 512^3 mask, 16% of the
+// 128^3 one have such a lane) fetch the second one in a branch of their own.
+// idx(i): the index of the source of direction i; ld(k): the value at index k. own is the node's own
+// value (the source of the x-shifted directions of the node's own row). SOLID_OWN: where x - c_i is
+// solid the node's own value stands in (state vectors, whose solid sources are bounce-back);
+// otherwise every neighbour has a value of its own (rho^N, extrapolated into solids). need(i): false
+// (a constant) for a direction whose value is neither used nor the centre of one that is.
 // Every 64 consecutive threads of a launch hold consecutive fluid ids.
-template <bool SOLID_OWN, class T, class Load>
-__device__ inline void row_shared(const Nbr& nb, uint32_t inf, const T& own, Load ld, T out[18]) {
-  using D = D3Q19;
+// row_gather issues the gathers; row_resolve waits for them and moves the values across lanes, so a
+// caller can put its other loads in flight between the two.
+constexpr int kRowPlus[5] = {0, 6, 7, 8, 9}, kRowMinus[5] = {1, 10, 11, 12, 13};  // directions (+1, r), (-1, r) of row r
+
+struct RowLanes {
+  bool below, above;  // lane l - 1 holds node x - 1 of this row (direction 0 pulls from x - 1), lane l + 1 node x + 1
+};
+__device__ inline RowLanes row_lanes(uint32_t inf) {
   const int lane = __lane_id();
-  // lane l - 1 holds node x - 1 of this row (direction 0 pulls from x - 1), lane l + 1 node x + 1
-  const bool below = !(inf & 1u) && nb.dxm == -1 && lane > 0;
-  const bool above = !((inf >> 1) & 1u) && nb.dxp == 1 && lane < 63;
-  // The gathers: partner directions (c_ix = 0) for every lane, x-shifted directions only where the
-  // neighbouring lane cannot supply them, all issued before any cross-lane move.
-  T gathered[18];
+  return {!(inf & (1u | (1u << kFaceShift))) && lane > 0, !(inf & (2u | (2u << kFaceShift))) && lane < 63};
+}
+
+template <bool SOLID_OWN, class T, class Index, class Load, class Need>
+__device__ inline void row_gather(const RowLanes& lanes, uint32_t inf, Index idx, Load ld, Need need, T out[18], T edge[5]) {
+  using D = D3Q19;
+  const bool below = lanes.below, above = lanes.above;
+  const uint32_t belowm = below ? ~0u : 0u, abovem = above ? ~0u : 0u;
 #pragma unroll
-  for (int i = 0; i < 18; ++i) {
-    const bool solid = SOLID_OWN && ((inf >> i) & 1u);
-    if (D::cx[i] == 0) {
-      out[i] = ld(i);
-    } else if (!solid && !(D::cx[i] > 0 ? below : above)) {
-      gathered[i] = ld(i);
+  for (int i = 0; i < 18; ++i)
+    if (D::cx[i] == 0 && need(i)) out[i] = ld(idx(i));
+#pragma unroll
+  for (int r = 0; r < 5; ++r) {
+    const int ip = kRowPlus[r], im = kRowMinus[r];
+    if (!need(ip)) continue;
+    const uint32_t lack_p = SOLID_OWN ? ~(belowm | bit_mask(inf, ip)) : ~belowm;
+    const uint32_t lack_m = SOLID_OWN ? ~(abovem | bit_mask(inf, im)) : ~abovem;
+    if (lack_p | lack_m) edge[r] = ld(blend(lack_p, idx(ip), idx(im)));
+  }
+}
+
+template <bool SOLID_OWN, class T, class Index, class Load, class Need>
+__device__ inline void row_resolve(const RowLanes& lanes, uint32_t inf, const T& own, Index idx, Load ld, Need need,
+                                   T out[18], const T edge[5]) {
+  const bool below = lanes.below, above = lanes.above;
+  const uint32_t belowm = below ? ~0u : 0u, abovem = above ? ~0u : 0u;
+#pragma unroll
+  for (int r = 0; r < 5; ++r) {
+    const int ip = kRowPlus[r], im = kRowMinus[r];
+    if (!need(ip)) continue;
+    const int m = yz_partner(ip);
+    const T base = (m < 0) ? own : out[m];
+    out[ip] = blend(belowm, lane_move<-1>(base), edge[r]);
+    out[im] = blend(abovem, lane_move<+1>(base), edge[r]);
+  }
+  if (!below && !above) {
+#pragma unroll
+    for (int r = 0; r < 5; ++r)
+      if (need(kRowPlus[r])) out[kRowMinus[r]] = ld(idx(kRowMinus[r]));
+  }
+  if (SOLID_OWN) {
+#pragma unroll
+    for (int r = 0; r < 5; ++r) {
+      const int ip = kRowPlus[r], im = kRowMinus[r];
+      if (!need(ip)) continue;
+      out[ip] = blend(bit_mask(inf, ip), own, out[ip]);
+      out[im] = blend(bit_mask(inf, im), own, out[im]);
     }
   }
-#pragma unroll
-  for (int i = 0; i < 18; ++i) {
-    if (D::cx[i] == 0) continue;
-    const int m = yz_partner(i);
-    const T base = (m < 0) ? own : out[m];
-    const T moved = (D::cx[i] > 0) ? lane_move<-1>(base) : lane_move<+1>(base);
-    const bool solid = SOLID_OWN && ((inf >> i) & 1u);
-    out[i] = solid ? own : ((D::cx[i] > 0 ? below : above) ? moved : gathered[i]);
-  }
+}
+
+template <bool SOLID_OWN, class T, class Index, class Load, class Need>
+__device__ inline void row_shared(uint32_t inf, const T& own, Index idx, Load ld, Need need, T out[18]) {
+  const RowLanes lanes = row_lanes(inf);
+  T edge[5];
+  row_gather<SOLID_OWN>(lanes, inf, idx, ld, need, out, edge);
+  row_resolve<SOLID_OWN>(lanes, inf, own, idx, ld, need, out, edge);
 }
 
 template <int P>
 struct StepArgs {
   using S = typename Prec<P>::S;
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   int nx, ny, nz, N;
   size_t ps;              // plane stride of the state and adjoint planes (>= fluid nodes)
   Geom geo;
-  const int* fluid;       // dense indices of the fluid nodes, in increasing order
-  const uint32_t* finfo;  // their info words
+  const ListNode* fluid;  // the fluid nodes, in increasing order
   int nfluid;
-  const int* ext;         // dense indices of the solid nodes whose colour is extrapolated
-  const uint32_t* einfo;  // their info words
+  const ListNode* ext;    // the solid nodes whose colour is extrapolated
   int next;
-  const int* fid;         // dense node -> fluid id (index into the state arrays), -1 for solid
+  const IdWord* ids;      // map from nodes to fluid ids (index into the state arrays)
   const int* order;       // optional launch order of the fluid-list tiles (null: list order)
   const uint32_t* info;
   // state in (pull source) and out
@@ -371,10 +478,24 @@ struct StepArgs {
 // significant bits of the storage apply to them and not to C itself. Population q of the node with
 // fluid id src:
 template <int P>
-__device__ inline typename Prec<P>::R ld_species(const StepArgs<P>& A, int q, int src) {
+__device__ inline typename Prec<P>::R species_value(const StepArgs<P>& A, int q, typename Prec<P>::Off src, typename Prec<P>::S s) {
   using R = typename Prec<P>::R;
   const R w = R(D3Q7::w(q));
-  return Prec<P>::ld(A.gin[size_t(q) * A.ps + src], P >= 2 ? w * A.cin[src] : w, A.inv_gscale);
+  return Prec<P>::ld(s, Prec<P>::deviations ? w * ldx<typename Prec<P>::Off>(A.cin, src) : w, A.inv_gscale);
+}
+template <int P>
+__device__ inline typename Prec<P>::R ld_species(const StepArgs<P>& A, int q, typename Prec<P>::Off src) {
+  return species_value(A, q, src, ldx<typename Prec<P>::Off>(A.gin + size_t(q) * A.ps, src));
+}
+
+// The stored population that a pull along direction i reads from plane i at src, or from the plane
+// of the opposite direction where bit i of inf is set (bounce-back; src is then the node itself).
+// The two planes share one uniform base, that of the lower one, and the select adds their distance.
+template <class Off, class S>
+__device__ inline S ld_pull(const S* planes, size_t ps, int i, int opp, uint32_t src, uint32_t inf) {
+  const int lo = i < opp ? i : opp, dist = i < opp ? opp - i : i - opp;
+  const uint32_t upper = bit_mask(i < opp ? inf : ~inf, i);
+  return ldx<Off>(planes + size_t(lo) * ps, Off(src) + (Off(int64_t(int32_t(upper))) & Off(size_t(dist) * ps)));
 }
 
 // Sum of the per-workgroup partials (5 planes of nparts) by one workgroup of kBlock threads, in
@@ -422,45 +543,79 @@ __global__ __launch_bounds__(kBlock) void k_finish_reduce(const double* partials
 }
 
 // ---------------------------------------------------------------------------------------------
-// colour: rho^N = (rho^r - rho^p)/rho^m from the pulled populations. The pull-source ids come
-// from pull_sources (most of them derived from a neighbour's rank) and the sources' colour
-// scalars from row_shared (one gather per row triple); the pass is bound by its gathers' address
-// and cache-line work, not by its bytes (102 VGPRs, four waves per SIMD).
+// colour: rho^N = (rho^r - rho^p)/rho^m from the pulled populations. Two dependent round trips (the
+// id map, then every gather of the node: nine rows of colour scalars, the rows' edges and 19
+// populations, all in flight together). Bound by the cache requests of its gathers, not by
+// instructions or occupancy: with every source replaced by the node itself (the same loads, aligned)
+// it takes 417 us on a 512 x 512 x 128 porous lattice (18.5M fluid nodes, FP32), as a plain read of
+// its planes does, and with the real sources 576 us (118 B per node, 3.8 TB/s; 650 us before the
+// id words, the merged row edges and the 32-bit offsets); 128^3 FP32 37.2 -> 34.8 us, FP64 84.8 ->
+// 69.6 us. 94 VGPRs, five waves per SIMD; holding it to four costs 4%.
 // ---------------------------------------------------------------------------------------------
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_colour(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
   if (A.red_out && blockIdx.x == 0) reduce_partials(A.red_in, A.red_n, A.red_out);
-  const int t = fluid_tile(A) * kBlock + threadIdx.x;
-  if (t >= A.nfluid) return;
-  const int n = A.fluid[t];
-  const uint32_t inf = A.finfo[t];
-  const Nbr nb = make_nbr(n, A.geo);
-  int sid[18];
-  pull_sources(A.fid, nb, t, inf, sid);
-  const typename V4<R>::T own = ld4(A.ain, t);
-  typename V4<R>::T avs[18];  // (e, v) at the sources (own where solid: bounce-back)
-  row_shared<true>(nb, inf, own, [&](int i) { return ld4(A.ain, sid[i]); }, avs);
+  using Off = typename Prec<P>::Off;
+  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.nfluid)) return;
+  const ListNode ln = ldx<Off>(A.fluid, t);
+  const int n = ln.node;
+  const uint32_t inf = ln.info;
+  const Nbr nb = make_nbr(n, inf, A.geo);
+  uint32_t sid[18];
+  pull_sources<Off>(A.ids, nb, t, inf, sid);
+  const typename V4<R>::T own = ld4<Off>(A.ain, t);
+  typename V4<R>::T avs[18], edge[5];  // (e, v) at the sources
+  const RowLanes lanes = row_lanes(inf);
+  const auto idx = [&](int i) { return sid[i]; };
+  const auto ld = [&](uint32_t k) { return ld4<Off>(A.ain, k); };
+  const auto all = [](int) { return true; };
+  row_gather<true>(lanes, inf, idx, ld, all, avs, edge);
+  typename Prec<P>::S s[19];
+#pragma unroll
+  for (int i = 0; i < 18; ++i) s[i] = ld_pull<Off>(A.fin, A.ps, i, D::opp[i], sid[i], inf);
+  s[18] = ldx<Off>(A.fin + 18 * A.ps, t);
+  __builtin_amdgcn_sched_barrier(0);  // every load of the node in flight before the first wait
+#pragma unroll
+  for (int i = 0; i < 18; ++i)
+    if (D::cx[i] == 0) use_whole(avs[i]);
+#pragma unroll
+  for (int r = 0; r < 5; ++r) use_whole(edge[r]);
+  row_resolve<false>(lanes, inf, own, idx, ld, all, avs, edge);
+  // c_i . v, without the terms of zero components
+  const auto along = [](int i, const typename V4<R>::T& av) {
+    R s = 0;
+    bool first = true;
+    if (D::cx[i]) { s = D::cx[i] > 0 ? av.y : -av.y; first = false; }
+    if (D::cy[i]) { const R w = D::cy[i] > 0 ? av.z : -av.z; s = first ? w : s + w; first = false; }
+    if (D::cz[i]) { const R w = D::cz[i] > 0 ? av.w : -av.w; s = first ? w : s + w; }
+    return s;
+  };
   R rm = 0, rr = 0, rp = 0;
 #pragma unroll
-  for (int i = 0; i < 19; ++i) {
-    const bool bb = (i < 18) && ((inf >> i) & 1u);
-    const int src = (i == 18) ? t : sid[i];
-    const int q = bb ? D::opp[i] : i;
-    const R sgn = bb ? R(-1) : R(1);  // c_q = sgn * c_i
-    const R fm = Prec<P>::ld(A.fin[size_t(q) * A.ps + src], R(D::w(i)), A.inv_scale);
-    const typename V4<R>::T av = (i == 18) ? own : avs[i];
-    const R cv = R(D::cx[i]) * av.y + R(D::cy[i]) * av.z + R(D::cz[i]) * av.w;
+  for (int i = 0; i < 18; ++i) {
+    const R fm = Prec<P>::ld(s[i], R(D::w(i)), A.inv_scale);
+    // where x - c_i is solid, the node's own population of direction opp(i) bounced back
+    const uint32_t bb = bit_mask(inf, i);
+    const R e = D::cx[i] ? blend(bb, own.x, avs[i].x) : avs[i].x;  // at c_ix = 0 the gathered source is the node itself
+    const R cv = blend(bb, along(D::opp[i], own), along(i, avs[i]));
     R a, b;
-    unpack_frac(av.x, a, b);
-    const R kv = R(D::w_over_len(i)) * sgn * cv;
+    unpack_frac(e, a, b);
+    const R kv = rounded_product(R(D::w_over_len(i)), cv);
     rm += fm;
     rr += a * fm + kv;
     rp += b * fm - kv;
   }
-  A.rhoN[n] = rn_pack(rr, rp, R(1) / rm);
-  if (A.rm_out) A.rm_out[n] = rm;
+  const R f0 = Prec<P>::ld(s[18], R(D::w(18)), A.inv_scale);
+  R a0, b0;
+  unpack_frac(own.x, a0, b0);
+  rm += f0;
+  rr += rounded_product(a0, f0);
+  rp += rounded_product(b0, f0);
+  refx<Off>(A.rhoN, uint32_t(n)) = rn_pack(rr, rp, R(1) / rm);
+  if (A.rm_out) refx<Off>(A.rm_out, uint32_t(n)) = rm;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -470,11 +625,13 @@ template <int P>
 __global__ __launch_bounds__(kBlock) void k_extrap(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
-  const int t = logical_block() * kBlock + threadIdx.x;
-  if (t >= A.next) return;
-  const int n = A.ext[t];
-  const uint32_t inf = A.einfo[t];
-  const Nbr nb = make_nbr(n, A.geo);
+  using Off = typename Prec<P>::Off;
+  const uint32_t t = uint32_t(logical_block()) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.next)) return;
+  const ListNode ln = ldx<Off>(A.ext, t);
+  const int n = ln.node;
+  const uint32_t inf = ln.info;
+  const Nbr nb = make_nbr(n, inf, A.geo);
   // All 18 loads are issued before any is used, so their latencies overlap; a direction without a
   // fluid neighbour loads nothing (its lanes are masked off, which spares the address units; reading
   // the node's own entry instead made the pass 11% slower at 128^3).
@@ -482,7 +639,7 @@ __global__ __launch_bounds__(kBlock) void k_extrap(StepArgs<P> A) {
 #pragma unroll
   for (int i = 0; i < 18; ++i) {
     qv[i] = R(0);
-    if ((inf >> i) & 1u) qv[i] = A.rhoN[nb.at(D::cx[i], D::cy[i], D::cz[i])];
+    if ((inf >> i) & 1u) qv[i] = ldx<Off>(A.rhoN, uint32_t(nb.at(D::cx[i], D::cy[i], D::cz[i])));
   }
   // Weighted sums of the offsets q and of the sides s separately; -0 as the start keeps the
   // sign of an all-(-0) sum.
@@ -495,10 +652,10 @@ __global__ __launch_bounds__(kBlock) void k_extrap(StepArgs<P> A) {
     den = use ? den + R(D::w(i)) : den;
   }
   if (ns == den || ns == -den) {
-    A.rhoN[n] = nq / den;  // all neighbours on one side: the average keeps that side
+    refx<Off>(A.rhoN, uint32_t(n)) = nq / den;  // all neighbours on one side: the average keeps that side
   } else {
     const R v = (ns + nq) / den;
-    A.rhoN[n] = R(2) * pack_frac(R(0.5) * (R(1) + v), R(0.5) * (R(1) - v));
+    refx<Off>(A.rhoN, uint32_t(n)) = R(2) * pack_frac(R(0.5) * (R(1) + v), R(0.5) * (R(1) - v));
   }
 }
 
@@ -563,18 +720,22 @@ template <int P>
 __global__ __launch_bounds__(kBlock) void k_normal(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
-  const int t = logical_block() * kBlock + threadIdx.x;
-  if (t >= A.nfluid) return;
-  const int n = A.fluid[t];
-  const uint32_t inf = A.finfo[t];
-  const Nbr nb = make_nbr(n, A.geo);
+  using Off = typename Prec<P>::Off;
+  const uint32_t t = uint32_t(logical_block()) * kBlock + threadIdx.x;
+  if (t >= uint32_t(A.nfluid)) return;
+  const ListNode ln = ldx<Off>(A.fluid, t);
+  const int n = ln.node;
+  const uint32_t inf = ln.info;
+  const Nbr nb = make_nbr(n, inf, A.geo);
   // The wetting data of a wetting node is loaded with the neighbours' colours, not after the
   // gradient: one memory round trip for the node instead of two.
   typename V4<R>::T wv;
   wv.x = wv.y = wv.z = wv.w = R(0);
-  if (inf & kWet) wv = ld4(A.wet, t);
+  if (inf & kWet) wv = ld4<Off>(A.wet, t);
   R src[18];  // rho^N at x - c_i (solid neighbours hold their extrapolated colour)
-  row_shared<false>(nb, inf, A.rhoN[n], [&](int i) { return A.rhoN[nb.at(-D::cx[i], -D::cy[i], -D::cz[i])]; }, src);
+  row_shared<false>(inf, ldx<Off>(A.rhoN, uint32_t(n)),
+                    [&](int i) { return uint32_t(nb.at(-D::cx[i], -D::cy[i], -D::cz[i])); },
+                    [&](uint32_t k) { return ldx<Off>(A.rhoN, k); }, [](int) { return true; }, src);
   R d[9];
 #pragma unroll
   for (int j = 0; j < 9; ++j) {
@@ -584,8 +745,8 @@ __global__ __launch_bounds__(kBlock) void k_normal(StepArgs<P> A) {
   R nv[3], len, raw[3];
   bool raw_set;
   normal_from_pairs<R>(d, inf, wv, A.eps, nv, len, raw, raw_set);
-  if (raw_set && A.nraw) st4(A.nraw, t, raw[0], raw[1], raw[2], R(0));
-  st4(A.nst, t, nv[0], nv[1], nv[2], len);
+  if (raw_set && A.nraw) st4<Off>(A.nraw, t, raw[0], raw[1], raw[2], R(0));
+  st4<Off>(A.nst, t, nv[0], nv[1], nv[2], len);
 }
 
 // T^{-1} k* of Appendix A (eq. back_transformation_vector), regrouped with common
@@ -664,28 +825,24 @@ __device__ inline void block_reduce5(double s[5], double* partials) { block_redu
 // where x - c_i is solid (sid: the sources' fluid ids, t for bounce-back), and likewise the species
 // (the outflow plane takes its own S_1: zero gradient).
 template <int P>
-__device__ inline void pull_node(const StepArgs<P>& A, int t, uint32_t inf, const int sid[18],
+__device__ inline void pull_node(const StepArgs<P>& A, uint32_t t, uint32_t inf, const uint32_t sid[18],
                                  typename Prec<P>::R f[19], typename Prec<P>::R g[7]) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
 #pragma unroll
-  for (int i = 0; i < 19; ++i) {
-    const bool bb = (i < 18) && ((inf >> i) & 1u);
-    const int src = (i < 18) ? sid[i] : t;
-    const int q = bb ? D::opp[i] : i;
-    f[i] = Prec<P>::ld(A.fin[size_t(q) * A.ps + src], R(D::w(i)), A.inv_scale);
-  }
+  for (int i = 0; i < 18; ++i)
+    f[i] = Prec<P>::ld(ld_pull<Off>(A.fin, A.ps, i, D::opp[i], sid[i], inf), R(D::w(i)), A.inv_scale);
+  f[18] = Prec<P>::ld(ldx<Off>(A.fin + 18 * A.ps, t), R(D::w(18)), A.inv_scale);
 #pragma unroll
   for (int i = 0; i < 7; ++i) g[i] = R(0);
   if (A.species) {
-    const bool outlet = inf & kOutlet;
+    const bool outlet = inf & kOutlet;  // zero-gradient outflow: the node's own S_1
+    const uint32_t ginf = outlet ? inf & ~2u : inf;
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-      const bool own = (i == 1 && outlet);  // zero-gradient outflow: the node's own S_1
-      const bool bb = !own && ((inf >> i) & 1u);
-      const int src = own ? t : sid[i];
-      const int q = own ? 1 : (bb ? D3Q7::opp[i] : i);
-      g[i] = ld_species(A, q, src);
+      const uint32_t src = (i == 1 && outlet) ? t : sid[i];
+      g[i] = species_value(A, i, src, ld_pull<Off>(A.gin, A.ps, i, D3Q7::opp[i], src, ginf));
     }
     g[6] = ld_species(A, 6, t);
   }
@@ -729,11 +886,12 @@ __device__ inline R curvature_hg(const typename V4<R>::T& nsv, R eps, NbrN nbr) 
 // (rn_value form); cur: (n*, H |G|) of x (n* = 0 where x has no normal). MOM writes the level-t
 // fields instead.
 template <int P, bool MOM>
-__device__ inline void collide_node(const StepArgs<P>& A, int t, int n, uint32_t inf,
+__device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uint32_t inf,
                                     const typename Prec<P>::R f[19], const typename Prec<P>::R g[7],
                                     typename Prec<P>::R rn, const typename V4<typename Prec<P>::R>::T& cur,
                                     double red5[5]) {
   using R = typename Prec<P>::R;
+  using Off = typename Prec<P>::Off;
   using D = D3Q19;
   const size_t N = A.N;
   // Moments (same summation order as k_colour, so rho^m agrees bit for bit).
@@ -835,8 +993,8 @@ __device__ inline void collide_node(const StepArgs<P>& A, int t, int n, uint32_t
     const R vc = keep * A.beta * rr * rp * irm;
     const R v0 = has_n ? vc * n0 : R(0), v1 = has_n ? vc * n1 : R(0), v2 = has_n ? vc * n2 : R(0);
 #pragma unroll
-    for (int i = 0; i < 19; ++i) A.fout[size_t(i) * A.ps + t] = Prec<P>::st(fs[i], R(D::w(i)), A.scale);
-    st4(A.aout, t, aout, v0, v1, v2);
+    for (int i = 0; i < 19; ++i) refx<Off>(A.fout + size_t(i) * A.ps, t) = Prec<P>::st(fs[i], R(D::w(i)), A.scale);
+    st4<Off>(A.aout, t, aout, v0, v1, v2);
     bool ok = finite(fsum) && finite(aout) && finite(v0 + v1 + v2) && finite(rr) && finite(rp);
     if (A.species) {
       // BGK towards g^eq = w C (1 + 4 c.u_phys); at the inlet the populations are replaced by
@@ -853,10 +1011,11 @@ __device__ inline void collide_node(const StepArgs<P>& A, int t, int n, uint32_t
         go[i] = (gi + (geq - gi) * A.inv_tau_c) * sink;
         gs += go[i];
       }
-      if (P >= 2) A.cout[t] = gs;  // the deviation reference of the stored populations
+      if (Prec<P>::deviations) refx<Off>(A.cout, t) = gs;  // the deviation reference of the stored populations
 #pragma unroll
       for (int i = 0; i < 7; ++i)
-        A.gout[size_t(i) * A.ps + t] = Prec<P>::st(go[i], P >= 2 ? R(D3Q7::w(i)) * gs : R(D3Q7::w(i)), A.gscale);
+        refx<Off>(A.gout + size_t(i) * A.ps, t) =
+            Prec<P>::st(go[i], Prec<P>::deviations ? R(D3Q7::w(i)) * gs : R(D3Q7::w(i)), A.gscale);
       ok = ok && finite(gs);
     }
     red5[0] += double(rr);
@@ -877,25 +1036,28 @@ template <int P, bool MOM>
 __global__ __launch_bounds__(kBlock) void k_collide(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
-  const int t = fluid_tile(A) * kBlock + threadIdx.x;
+  using Off = typename Prec<P>::Off;
+  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
   double red5[5] = {0, 0, 0, 0, 0};
-  const int n = (t < A.nfluid) ? A.fluid[t] : 0;
-  const uint32_t inf = (t < A.nfluid) ? A.finfo[t] : 0u;
-  if (inf & kFluid) {
-    const Nbr nb = make_nbr(n, A.geo);
+  if (t < uint32_t(A.nfluid)) {
+    const ListNode ln = ldx<Off>(A.fluid, t);
+    const int n = ln.node;
+    const uint32_t inf = ln.info;
+    const Nbr nb = make_nbr(n, inf, A.geo);
     // All loads of the node first (pull of f^m and g with halfway bounce-back, rho^N, the node's
     // and its neighbours' realigned normals), so that one memory round trip covers them.
-    int sid[18];  // fluid ids of the pull sources (own id for bounce-back)
-    pull_sources(A.fid, nb, t, inf, sid);
+    uint32_t sid[18];  // fluid ids of the pull sources (own id for bounce-back)
+    pull_sources<Off>(A.ids, nb, t, inf, sid);
     R f[19], g[7];
     pull_node(A, t, inf, sid, f, g);
-    const R rn = A.rhoN[n];
+    const R rn = ldx<Off>(A.rhoN, uint32_t(n));
     // The node's and its neighbours' realigned normals; x + c_i is the pull source of direction
     // opp(i), the node's own id where it is solid, which is the value the curvature takes for a
     // solid neighbour.
-    const typename V4<R>::T nsv = ld4(A.nst, t);
+    const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
     typename V4<R>::T srcv[18];
-    row_shared<true>(nb, inf, nsv, [&](int i) { return ld4(A.nst, sid[i]); }, srcv);
+    row_shared<true>(inf, nsv, [&](int i) { return sid[i]; }, [&](uint32_t k) { return ld4<Off>(A.nst, k); },
+                     [](int) { return true; }, srcv);
     typename V4<R>::T cur = nsv;
     cur.w = curvature_hg<R>(nsv, A.eps, [&](int i) { return srcv[D::opp[i]]; });
     collide_node<P, MOM>(A, t, n, inf, f, g, rn, cur, red5);
@@ -915,14 +1077,16 @@ template <int P>
 __global__ __launch_bounds__(kBlock) void k_state_sums(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
-  const int t = logical_block() * kBlock + threadIdx.x;
+  using Off = typename Prec<P>::Off;
+  const uint32_t t = uint32_t(logical_block()) * kBlock + threadIdx.x;
   double red5[5] = {0, 0, 0, 0, 0};
-  if (t < A.nfluid) {
+  if (t < uint32_t(A.nfluid)) {
     R a, b;
-    unpack_frac(ld4(A.ain, t).x, a, b);
+    unpack_frac(ld4<Off>(A.ain, t).x, a, b);
     R s = 0;
 #pragma unroll
-    for (int i = 0; i < 19; ++i) s += Prec<P>::ld(A.fin[size_t(i) * A.ps + t], R(D::w(i)), A.inv_scale);
+    for (int i = 0; i < 19; ++i)
+      s += Prec<P>::ld(ldx<Off>(A.fin + size_t(i) * A.ps, t), R(D::w(i)), A.inv_scale);
     R C = 0;
     if (A.species)
 #pragma unroll
@@ -946,11 +1110,11 @@ __global__ __launch_bounds__(kBlock) void k_expand(StepArgs<P> A, typename Prec<
   const int n = logical_block() * kBlock + threadIdx.x;
   if (n >= A.N) return;
   const size_t N = A.N;
-  const int fi = A.fid[n];
-  const bool fluid = fi >= 0;
+  const bool fluid = A.info[n] & kFluid;
+  const size_t fi = fluid ? fluid_id(A.ids, n) : 0;
   typename V4<R>::T av;
   av.x = av.y = av.z = av.w = R(0);
-  if (fluid) av = ld4(A.ain, fi);
+  if (fluid) av = ld4<size_t>(A.ain, fi);
   const R v0 = av.y, v1 = av.z, v2 = av.w;
   R a, b;
   unpack_frac(av.x, a, b);
