@@ -29,7 +29,7 @@
 // one 4-vector per fluid node. Two state buffers are used alternately (pull from one, write the
 // other), so no kernel reads what another thread of the same launch writes.
 //
-// One step is four launches (each one thread per node):
+// One step is four launches (each one thread per node; one, collide, where sigma = beta = 0):
 //   colour   pull f^m, a, v -> rho^N at fluid nodes             (eqs. moments_components, color_function)
 //   extrap   rho^N into solid nodes next to fluid               (eq. color_lattice_weighted_average)
 //   normal   isotropic gradient, unit normal, Akai realignment   (eqs. finite_difference_scheme,
@@ -91,6 +91,15 @@ __device__ inline void st4(R* p, Off n, R x, R y, R z, R w) {
 // otherwise split, and a gather costs by the instruction and its cache lines, not by the words.
 __device__ inline void use_whole(const float4& v) { asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w)); }
 __device__ inline void use_whole(const double4& v) { asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w)); }
+
+template <class T>
+__device__ inline void use_whole(const T avs[18], const T edge[5]) {
+#pragma unroll
+  for (int i = 0; i < 18; ++i)
+    if (D3Q19::cx[i] == 0) use_whole(avs[i]);
+#pragma unroll
+  for (int r = 0; r < 5; ++r) use_whole(edge[r]);
+}
 
 // a b rounded, never fused into a following sum.
 template <class R>
@@ -498,6 +507,35 @@ __device__ inline S ld_pull(const S* planes, size_t ps, int i, int opp, uint32_t
   return ldx<Off>(planes + size_t(lo) * ps, Off(src) + (Off(int64_t(int32_t(upper))) & Off(size_t(dist) * ps)));
 }
 
+// Pull of fluid node t with halfway bounce-back: f^m_i from S_t at x - c_i, or S_t,opp(i) at x
+// where x - c_i is solid (sid: the sources' fluid ids, t for bounce-back), as stored; and likewise the
+// species (the outflow plane takes its own S_1: zero gradient).
+template <int P>
+__device__ inline void ld_populations(const StepArgs<P>& A, uint32_t t, uint32_t inf, const uint32_t sid[18],
+                                      typename Prec<P>::S s[19]) {
+  using Off = typename Prec<P>::Off;
+#pragma unroll
+  for (int i = 0; i < 18; ++i) s[i] = ld_pull<Off>(A.fin, A.ps, i, D3Q19::opp[i], sid[i], inf);
+  s[18] = ldx<Off>(A.fin + 18 * A.ps, t);
+}
+template <int P>
+__device__ inline void pull_species(const StepArgs<P>& A, uint32_t t, uint32_t inf, const uint32_t sid[18],
+                                    typename Prec<P>::R g[7]) {
+  using Off = typename Prec<P>::Off;
+#pragma unroll
+  for (int i = 0; i < 7; ++i) g[i] = 0;
+  if (A.species) {
+    const bool outlet = inf & kOutlet;  // zero-gradient outflow: the node's own S_1
+    const uint32_t ginf = outlet ? inf & ~2u : inf;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      const uint32_t src = (i == 1 && outlet) ? t : sid[i];
+      g[i] = species_value(A, i, src, ld_pull<Off>(A.gin, A.ps, i, D3Q7::opp[i], src, ginf));
+    }
+    g[6] = ld_species(A, 6, t);
+  }
+}
+
 // Sum of the per-workgroup partials (5 planes of nparts) by one workgroup of kBlock threads, in
 // a fixed order: strided per-thread sums, then wavefront shuffles, then the waves in order. Every
 // caller uses this one routine with the same thread count, so a step's sums do not depend on
@@ -552,6 +590,47 @@ __global__ __launch_bounds__(kBlock) void k_finish_reduce(const double* partials
 // id words, the merged row edges and the 32-bit offsets); 128^3 FP32 37.2 -> 34.8 us, FP64 84.8 ->
 // 69.6 us. 94 VGPRs, five waves per SIMD; holding it to four costs 4%.
 // ---------------------------------------------------------------------------------------------
+
+// rho^N (rn_value form) and rho^m of a node from its pulled populations fm(i) and the colour scalars
+// (e, v): own, and avs[i] of the node at x - c_i (of any node where that is solid and c_ix != 0; own
+// where it is solid and c_ix = 0). Every pass that forms rho^N calls this.
+template <class R, class Pop>
+__device__ inline R colour_of(uint32_t inf, const typename V4<R>::T& own, const typename V4<R>::T avs[18], Pop fm, R& rm_out) {
+  using D = D3Q19;
+  // c_i . v, without the terms of zero components
+  const auto along = [](int i, const typename V4<R>::T& av) {
+    R s = 0;
+    bool first = true;
+    if (D::cx[i]) { s = D::cx[i] > 0 ? av.y : -av.y; first = false; }
+    if (D::cy[i]) { const R w = D::cy[i] > 0 ? av.z : -av.z; s = first ? w : s + w; first = false; }
+    if (D::cz[i]) { const R w = D::cz[i] > 0 ? av.w : -av.w; s = first ? w : s + w; }
+    return s;
+  };
+  R rm = 0, rr = 0, rp = 0;
+#pragma unroll
+  for (int i = 0; i < 18; ++i) {
+    const R f = fm(i);
+    // where x - c_i is solid, the node's own population of direction opp(i) bounced back
+    const uint32_t bb = bit_mask(inf, i);
+    const R e = D::cx[i] ? blend(bb, own.x, avs[i].x) : avs[i].x;
+    const R cv = blend(bb, along(D::opp[i], own), along(i, avs[i]));
+    R a, b;
+    unpack_frac(e, a, b);
+    const R kv = rounded_product(R(D::w_over_len(i)), cv);
+    rm += f;
+    rr += a * f + kv;
+    rp += b * f - kv;
+  }
+  const R f0 = fm(18);
+  R a0, b0;
+  unpack_frac(own.x, a0, b0);
+  rm += f0;
+  rr += rounded_product(a0, f0);
+  rp += rounded_product(b0, f0);
+  rm_out = rm;
+  return rn_pack(rr, rp, R(1) / rm);
+}
+
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_colour(StepArgs<P> A) {
   using R = typename Prec<P>::R;
@@ -574,47 +653,13 @@ __global__ __launch_bounds__(kBlock) void k_colour(StepArgs<P> A) {
   const auto all = [](int) { return true; };
   row_gather<true>(lanes, inf, idx, ld, all, avs, edge);
   typename Prec<P>::S s[19];
-#pragma unroll
-  for (int i = 0; i < 18; ++i) s[i] = ld_pull<Off>(A.fin, A.ps, i, D::opp[i], sid[i], inf);
-  s[18] = ldx<Off>(A.fin + 18 * A.ps, t);
+  ld_populations(A, t, inf, sid, s);
   __builtin_amdgcn_sched_barrier(0);  // every load of the node in flight before the first wait
-#pragma unroll
-  for (int i = 0; i < 18; ++i)
-    if (D::cx[i] == 0) use_whole(avs[i]);
-#pragma unroll
-  for (int r = 0; r < 5; ++r) use_whole(edge[r]);
+  use_whole(avs, edge);
   row_resolve<false>(lanes, inf, own, idx, ld, all, avs, edge);
-  // c_i . v, without the terms of zero components
-  const auto along = [](int i, const typename V4<R>::T& av) {
-    R s = 0;
-    bool first = true;
-    if (D::cx[i]) { s = D::cx[i] > 0 ? av.y : -av.y; first = false; }
-    if (D::cy[i]) { const R w = D::cy[i] > 0 ? av.z : -av.z; s = first ? w : s + w; first = false; }
-    if (D::cz[i]) { const R w = D::cz[i] > 0 ? av.w : -av.w; s = first ? w : s + w; }
-    return s;
-  };
-  R rm = 0, rr = 0, rp = 0;
-#pragma unroll
-  for (int i = 0; i < 18; ++i) {
-    const R fm = Prec<P>::ld(s[i], R(D::w(i)), A.inv_scale);
-    // where x - c_i is solid, the node's own population of direction opp(i) bounced back
-    const uint32_t bb = bit_mask(inf, i);
-    const R e = D::cx[i] ? blend(bb, own.x, avs[i].x) : avs[i].x;  // at c_ix = 0 the gathered source is the node itself
-    const R cv = blend(bb, along(D::opp[i], own), along(i, avs[i]));
-    R a, b;
-    unpack_frac(e, a, b);
-    const R kv = rounded_product(R(D::w_over_len(i)), cv);
-    rm += fm;
-    rr += a * fm + kv;
-    rp += b * fm - kv;
-  }
-  const R f0 = Prec<P>::ld(s[18], R(D::w(18)), A.inv_scale);
-  R a0, b0;
-  unpack_frac(own.x, a0, b0);
-  rm += f0;
-  rr += rounded_product(a0, f0);
-  rp += rounded_product(b0, f0);
-  refx<Off>(A.rhoN, uint32_t(n)) = rn_pack(rr, rp, R(1) / rm);
+  R rm;
+  const R q = colour_of<R>(inf, own, avs, [&](int i) { return Prec<P>::ld(s[i], R(D::w(i)), A.inv_scale); }, rm);
+  refx<Off>(A.rhoN, uint32_t(n)) = q;
   if (A.rm_out) refx<Off>(A.rm_out, uint32_t(n)) = rm;
 }
 
@@ -821,33 +866,6 @@ __device__ inline void block_reduce5_n(double s[5], double* partials) {
 
 __device__ inline void block_reduce5(double s[5], double* partials) { block_reduce5_n<kBlock>(s, partials); }
 
-// Pull of fluid node t with halfway bounce-back: f^m_i from S_t at x - c_i, or S_t,opp(i) at x
-// where x - c_i is solid (sid: the sources' fluid ids, t for bounce-back), and likewise the species
-// (the outflow plane takes its own S_1: zero gradient).
-template <int P>
-__device__ inline void pull_node(const StepArgs<P>& A, uint32_t t, uint32_t inf, const uint32_t sid[18],
-                                 typename Prec<P>::R f[19], typename Prec<P>::R g[7]) {
-  using R = typename Prec<P>::R;
-  using Off = typename Prec<P>::Off;
-  using D = D3Q19;
-#pragma unroll
-  for (int i = 0; i < 18; ++i)
-    f[i] = Prec<P>::ld(ld_pull<Off>(A.fin, A.ps, i, D::opp[i], sid[i], inf), R(D::w(i)), A.inv_scale);
-  f[18] = Prec<P>::ld(ldx<Off>(A.fin + 18 * A.ps, t), R(D::w(18)), A.inv_scale);
-#pragma unroll
-  for (int i = 0; i < 7; ++i) g[i] = R(0);
-  if (A.species) {
-    const bool outlet = inf & kOutlet;  // zero-gradient outflow: the node's own S_1
-    const uint32_t ginf = outlet ? inf & ~2u : inf;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      const uint32_t src = (i == 1 && outlet) ? t : sid[i];
-      g[i] = species_value(A, i, src, ld_pull<Off>(A.gin, A.ps, i, D3Q7::opp[i], src, ginf));
-    }
-    g[6] = ld_species(A, 6, t);
-  }
-}
-
 // H |G| at fluid node x: the curvature H = -(tr J - n.J.n) (eq. interface_curvature) with
 // J_ab = 3 sum_i w_i c_ib n*_a(x + c_i), times the gradient magnitude |G| of x; zero where
 // |G| <= eps (no normal). nsv: (n*, |G|) of x; nbr(i): (n*, |G|) at x + c_i, or of x itself where
@@ -1031,35 +1049,69 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
 // instead (lbm_moments) and leaves the state untouched. Four waves per SIMD in FP32, FP16 and BF16
 // (at most 128 VGPRs, no spills; a five-wave bound made the 2-byte storages spill and run 11%
 // slower at 512^3); FP64 runs fewer.
+//
+// IFACE = true: rho^N and the realigned normals come from the colour and normal passes. A wave none
+// of whose nodes has |G| > eps skips its neighbours' normals: H is zero there whatever they are (the
+// own (n*, |G|) is loaded with the list entry, so the test costs no round trip; the sweep's 128^3
+// set-up, with interfaces round eight nucleation sites, 43 -> 40 us, waves without such nodes the same). IFACE = false, chosen
+// when sigma = beta = 0: neither the force nor the recolouring uses a normal, rho^N is needed at the
+// node alone, and this one kernel is the whole step, forming rho^N from its own pull.
 // ---------------------------------------------------------------------------------------------
-template <int P, bool MOM>
+template <int P, bool MOM, bool IFACE>
 __global__ __launch_bounds__(kBlock) void k_collide(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
   using Off = typename Prec<P>::Off;
+  if (!IFACE && A.red_out && blockIdx.x == 0) reduce_partials(A.red_in, A.red_n, A.red_out);
   const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
   double red5[5] = {0, 0, 0, 0, 0};
   if (t < uint32_t(A.nfluid)) {
     const ListNode ln = ldx<Off>(A.fluid, t);
+    // (n*, |G|) of the node, or its colour scalars (e, v)
+    const R* vec = IFACE ? A.nst : A.ain;
+    const typename V4<R>::T own = ld4<Off>(vec, t);
     const int n = ln.node;
     const uint32_t inf = ln.info;
     const Nbr nb = make_nbr(n, inf, A.geo);
-    // All loads of the node first (pull of f^m and g with halfway bounce-back, rho^N, the node's
-    // and its neighbours' realigned normals), so that one memory round trip covers them.
+    // All loads of the node together (pull of f^m and g with halfway bounce-back, rho^N, the
+    // neighbours' vectors), so that one memory round trip covers them.
     uint32_t sid[18];  // fluid ids of the pull sources (own id for bounce-back)
     pull_sources<Off>(A.ids, nb, t, inf, sid);
+    typename Prec<P>::S s[19];
+    ld_populations(A, t, inf, sid, s);
     R f[19], g[7];
-    pull_node(A, t, inf, sid, f, g);
-    const R rn = ldx<Off>(A.rhoN, uint32_t(n));
-    // The node's and its neighbours' realigned normals; x + c_i is the pull source of direction
-    // opp(i), the node's own id where it is solid, which is the value the curvature takes for a
-    // solid neighbour.
-    const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
-    typename V4<R>::T srcv[18];
-    row_shared<true>(inf, nsv, [&](int i) { return sid[i]; }, [&](uint32_t k) { return ld4<Off>(A.nst, k); },
-                     [](int) { return true; }, srcv);
-    typename V4<R>::T cur = nsv;
-    cur.w = curvature_hg<R>(nsv, A.eps, [&](int i) { return srcv[D::opp[i]]; });
+    pull_species(A, t, inf, sid, g);
+    R rn = 0;
+    if (IFACE) rn = ldx<Off>(A.rhoN, uint32_t(n));
+    const RowLanes lanes = row_lanes(inf);
+    const auto idx = [&](int i) { return sid[i]; };
+    const auto ld = [&](uint32_t k) { return ld4<Off>(vec, k); };
+    const auto all = [](int) { return true; };
+    typename V4<R>::T nbr[18], edge[5];
+    typename V4<R>::T cur;
+    cur.x = cur.y = cur.z = cur.w = 0;
+    if (IFACE) {
+      cur = own;
+      cur.w = R(0) * own.w;
+      if (__any(own.w > A.eps)) {
+        // x + c_i is the pull source of direction opp(i), the node's own id where it is solid, which
+        // is the value the curvature takes for a solid neighbour.
+        row_gather<true>(lanes, inf, idx, ld, all, nbr, edge);
+        row_resolve<true>(lanes, inf, own, idx, ld, all, nbr, edge);
+        cur.w = curvature_hg<R>(own, A.eps, [&](int i) { return nbr[D::opp[i]]; });
+      }
+#pragma unroll
+      for (int i = 0; i < 19; ++i) f[i] = Prec<P>::ld(s[i], R(D::w(i)), A.inv_scale);
+    } else {
+      row_gather<true>(lanes, inf, idx, ld, all, nbr, edge);
+      __builtin_amdgcn_sched_barrier(0);
+      use_whole(nbr, edge);
+      row_resolve<false>(lanes, inf, own, idx, ld, all, nbr, edge);
+#pragma unroll
+      for (int i = 0; i < 19; ++i) f[i] = Prec<P>::ld(s[i], R(D::w(i)), A.inv_scale);
+      R rm;
+      rn = colour_of<R>(inf, own, nbr, [&](int i) { return f[i]; }, rm);
+    }
     collide_node<P, MOM>(A, t, n, inf, f, g, rn, cur, red5);
   }
   if (!MOM) block_reduce5(red5, A.partials);
