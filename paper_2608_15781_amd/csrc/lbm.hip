@@ -114,7 +114,7 @@ Layout make_layout(const lbm_params& p) {
   L.lists[0] = o; o = align_up(o + sizeof(ListNode) * F);  // fluid nodes
   L.lists[1] = o; o = align_up(o + sizeof(ListNode) * E);  // solid nodes with extrapolated colour
   L.ids = o; o = align_up(o + sizeof(IdWord) * ((N + 31) / 32));  // node -> fluid id
-  L.counts = o; o = align_up(o + 4 * (size_t(nb) + 2));
+  L.counts = o; o = align_up(o + 2 * 4 * (size_t(nb) + 2));  // of the two launch lists
   L.order = o; o = align_up(o + 4 * size_t(nb));  // launch order of the fluid-list tiles
   L.state[0] = o; o = align_up(o + L.state_bytes);
   // The second state buffer comes last: lbm_init stages the host inputs there and in whatever
@@ -183,6 +183,7 @@ struct lbm_ctx {
   int nfluid, next;      // list lengths
   int nb_fluid, nb_ext;  // workgroups over each list (multiples of kXcd, 0 if empty)
   bool ordered;          // fluid-list tiles launched in the order stored at L.order
+  double* rows;          // pinned host memory: the ring rows of a chunk, written by k_finish_reduce
   void* static_scr;      // device address of the file-scope scratch array on this context's device
   char err[512];
   // Profiling: kEvents events per step of the current chunk (before the first kernel, after each).
@@ -394,21 +395,24 @@ __global__ void k_tile_heads(const ListNode* fluid, int ntiles, int* heads) {
   if (k < ntiles) heads[k] = fluid[size_t(k) * kBlock].node;
 }
 
-__global__ void k_scan_counts(int* counts, int nb) {
-  __shared__ int part[1024];
+// Exclusive scan of the counts in place; their sum to *total (pinned host memory).
+__global__ __launch_bounds__(1024) void k_scan_counts(int* counts, int nb, int* total) {
+  __shared__ int wave_total[16];
   const int chunk = (nb + 1023) / 1024;
-  const int b0 = threadIdx.x * chunk, b1 = min(nb, b0 + chunk);
+  const int b0 = min(nb, int(threadIdx.x) * chunk), b1 = min(nb, b0 + chunk);
   int sum = 0;
   for (int b = b0; b < b1; ++b) sum += counts[b];
-  part[threadIdx.x] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int i = 0; i < 1024; ++i) { const int v = part[i]; part[i] = run; run += v; }
-    counts[nb] = run;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int before = sum;  // inclusive over the wave's lanes
+  for (int d = 1; d < 64; d <<= 1) {
+    const int v = __shfl_up(before, d, 64);
+    if (lane >= d) before += v;
   }
+  if (lane == 63) wave_total[wave] = before;
   __syncthreads();
-  int run = part[threadIdx.x];
+  int run = before - sum;
+  for (int w = 0; w < wave; ++w) run += wave_total[w];
+  if (threadIdx.x == 1023) *total = run + sum;
   for (int b = b0; b < b1; ++b) { const int v = counts[b]; counts[b] = run; run += v; }
 }
 
@@ -494,7 +498,6 @@ StepArgs<P> make_args(lbm_ctx* c, int src_buf) {
   A.nst = reinterpret_cast<R*>(c->ws + L.nst);
   A.wet = reinterpret_cast<const R*>(c->ws + L.wet);
   A.partials = reinterpret_cast<double*>(c->ws + L.partials);
-  A.ring_row = reinterpret_cast<double*>(c->ws + L.ring);
   A.relax = R(1.0 - 1.0 / p.tau);
   A.inv_tau_c = p.species ? R(1.0 / p.tau_species) : R(1);
   A.sigma = R(p.sigma); A.beta = R(p.beta); A.xi = R(p.xi); A.c_in = R(p.c_inlet); A.eps = R(p.grad_eps);
@@ -530,8 +533,11 @@ template <int P>
 lbm_status enqueue_step(lbm_ctx* c, const StepArgs<P>& A, hipEvent_t* ev, bool fields, bool collide = true) {
   const dim3 block(kBlock), gf(c->nb_fluid), ge(c->nb_ext);
   const bool iface = uses_normals(c->p);
+  const dim3 gfirst(c->nb_fluid + (A.red_out ? kXcd : 0));  // of the pass that finishes the previous sums
+  StepArgs<P> AC = A;
+  if (!iface) AC.red_out = nullptr;
   if (ev) HIP_TRY(c, hipEventRecord(ev[0], c->stream));
-  if ((iface || fields) && c->nb_fluid) hipLaunchKernelGGL(k_colour<P>, gf, block, 0, c->stream, A);
+  if ((iface || fields) && c->nb_fluid) hipLaunchKernelGGL(k_colour<P>, iface ? gfirst : gf, block, 0, c->stream, AC);
   if (ev) HIP_TRY(c, hipEventRecord(ev[1], c->stream));
   if ((iface || fields) && c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
   if (ev) HIP_TRY(c, hipEventRecord(ev[2], c->stream));
@@ -541,12 +547,15 @@ lbm_status enqueue_step(lbm_ctx* c, const StepArgs<P>& A, hipEvent_t* ev, bool f
     if (iface)
       hipLaunchKernelGGL((k_collide<P, false, true>), gf, block, 0, c->stream, A);
     else
-      hipLaunchKernelGGL((k_collide<P, false, false>), gf, block, 0, c->stream, A);
+      hipLaunchKernelGGL((k_collide<P, false, false>), gfirst, block, 0, c->stream, A);
   }
   if (ev) HIP_TRY(c, hipEventRecord(ev[4], c->stream));
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
 }
+
+// How a step ends: with its sums in ring row `slot`, or enqueued without any.
+constexpr int kNoSums = -1;
 
 // The partial sums of the step in ring row `slot`. Two sets are used in turn, so that a step's
 // first workgroup can sum the previous step's set while the others write this step's.
@@ -555,20 +564,24 @@ double* step_partials(lbm_ctx* c, int slot) {
 }
 
 template <int P>
-lbm_status launch_step(lbm_ctx* c, int slot, bool timed, void* fields) {
+lbm_status launch_step(lbm_ctx* c, int slot, void* fields) {
   StepArgs<P> A = make_args<P>(c, c->cur);
   if (fields) use_fields<P>(c, A, fields);
-  double* ring = reinterpret_cast<double*>(c->ws + c->L.ring);
-  A.ring_row = ring + 5 * size_t(slot);
-  // The previous step's partials (one per collide workgroup) are summed by workgroup 0 of this
-  // step's first pass; the last step of a chunk is summed by launch_finish.
-  A.partials = step_partials(c, slot);
-  A.red_in = step_partials(c, slot + 1);
-  A.red_n = c->nb_fluid;
-  A.red_out = slot > 0 ? ring + 5 * size_t(slot - 1) : nullptr;
-  if (A.red_out && !c->nb_fluid)
-    hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream, A.red_in, A.red_n, A.red_out);
-  hipEvent_t* ev = (c->prof && timed) ? &c->ev[kEvents * size_t(slot)] : nullptr;
+  A.partials = nullptr;
+  hipEvent_t* ev = nullptr;
+  if (slot != kNoSums) {
+    // The previous step's partials (one per collide workgroup) are summed by workgroup 0 of this
+    // step's first pass; the last step of a chunk is summed by launch_finish.
+    double* ring = reinterpret_cast<double*>(c->ws + c->L.ring);
+    A.partials = step_partials(c, slot);
+    A.red_in = step_partials(c, slot + 1);
+    A.red_n = c->nb_fluid;
+    A.red_out = slot > 0 ? ring + 5 * size_t(slot - 1) : nullptr;
+    if (A.red_out && !c->nb_fluid)
+      hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream, A.red_in, A.red_n, ring, slot,
+                         static_cast<double*>(nullptr));
+    ev = c->prof ? &c->ev[kEvents * size_t(slot)] : nullptr;
+  }
   const lbm_status s = enqueue_step<P>(c, A, ev, fields != nullptr);
   if (s != LBM_OK) return s;
   c->cur = 1 - c->cur;
@@ -576,8 +589,8 @@ lbm_status launch_step(lbm_ctx* c, int slot, bool timed, void* fields) {
   return LBM_OK;
 }
 
-// One step from a caller's state buffer into another; the context's state is not touched. The
-// per-block partial sums are written to the workspace as in every step and never reduced.
+// One step from a caller's state buffer into another; the context's state is not touched and no
+// sums are formed.
 template <int P>
 lbm_status launch_step_from(lbm_ctx* c, const void* src, void* dst, void* fields) {
   using S = typename Prec<P>::S;
@@ -594,16 +607,15 @@ lbm_status launch_step_from(lbm_ctx* c, const void* src, void* dst, void* fields
   A.gout = db ? reinterpret_cast<S*>(db + c->L.g_off) : nullptr;
   A.cout = db ? reinterpret_cast<R*>(db + c->L.c_off) : nullptr;
   if (fields) use_fields<P>(c, A, fields);
-  A.ring_row = reinterpret_cast<double*>(c->ws + c->L.ring);
-  A.red_out = nullptr;
+  A.partials = nullptr;
   return enqueue_step<P>(c, A, nullptr, fields != nullptr, db != nullptr);  // no destination: the fields only
 }
 
-// Final reduction of the last step of a chunk (ring row `slot`).
+// Final reduction of the last step of a chunk (ring row `slot`), and rows 0 .. slot to the host.
 lbm_status launch_finish(lbm_ctx* c, int slot) {
   double* ring = reinterpret_cast<double*>(c->ws + c->L.ring);
   hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream,
-                     static_cast<const double*>(step_partials(c, slot)), c->nb_fluid, ring + 5 * size_t(slot));
+                     static_cast<const double*>(step_partials(c, slot)), c->nb_fluid, ring, slot + 1, c->rows);
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
 }
@@ -614,12 +626,9 @@ lbm_status launch_moments(lbm_ctx* c, void* rr, void* rp, void* rn, void* u, voi
   StepArgs<P> A = make_args<P>(c, c->cur);
   A.m_rr = static_cast<R*>(rr); A.m_rp = static_cast<R*>(rp); A.m_rn = static_cast<R*>(rn);
   A.m_u = static_cast<R*>(u); A.m_c = static_cast<R*>(cc);
-  const size_t N = c->N;
-  const size_t rb = sizeof(R);
-  for (void* ptr : {rr, rp, rn, cc})
-    if (ptr) HIP_TRY(c, hipMemsetAsync(ptr, 0, rb * N, c->stream));
-  if (u) HIP_TRY(c, hipMemsetAsync(u, 0, 3 * rb * N, c->stream));
   const dim3 gf(c->nb_fluid), ge(c->nb_ext), block(kBlock);
+  hipLaunchKernelGGL(k_clear_solids<R>, dim3((c->N + kBlock - 1) / kBlock), block, 0, c->stream, A.info, c->N, A.m_rr,
+                     A.m_rp, A.m_rn, A.m_u, A.m_c);
   if (!uses_normals(c->p)) {
     if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false>), gf, block, 0, c->stream, A);
   } else {
@@ -700,18 +709,18 @@ lbm_status launch_init(lbm_ctx* c, const uint8_t* d_solid, const uint8_t* d_reac
   IdWord* ids = reinterpret_cast<IdWord*>(c->ws + c->L.ids);
   const Geom geo = make_geom(p);
   // Launch lists: fluid nodes and solid nodes with extrapolated colour, in node order.
-  int* counts = reinterpret_cast<int*>(c->ws + c->L.counts);
   const uint32_t masks[2] = {kFluid, kExtrap};
-  int lens[2] = {0, 0};
+  int* lens = reinterpret_cast<int*>(c->rows);  // pinned
   for (int k = 0; k < 2; ++k) {
     ListNode* list = reinterpret_cast<ListNode*>(c->ws + c->L.lists[k]);
+    int* counts = reinterpret_cast<int*>(c->ws + c->L.counts) + k * size_t(c->L.nblocks + 2);
     hipLaunchKernelGGL(k_flag_count, dim3(gb), dim3(tb), 0, c->stream, info, c->N, masks[k], counts);
-    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, c->stream, counts, gb);
+    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, c->stream, counts, gb, lens + k);
     hipLaunchKernelGGL(k_flag_scatter, dim3(gb), dim3(tb), 0, c->stream, info, c->N, masks[k], counts, geo, list,
                        k == 0 ? ids : nullptr);
-    HIP_TRY(c, hipMemcpyAsync(&lens[k], counts + gb, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
+  HIP_TRY(c, hipGetLastError());
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->nfluid = lens[0];
   c->next = lens[1];
   hipLaunchKernelGGL(k_init_wet<R>, dim3(gb), dim3(tb), 0, c->stream, p.nx, p.ny, p.nz, d_solid, info,
@@ -754,10 +763,11 @@ lbm_status launch_state_sums(lbm_ctx* c, const void* state, double* out) {
   double* row = reinterpret_cast<double*>(c->ws + c->L.ring);
   if (c->nb_fluid)
     hipLaunchKernelGGL(k_state_sums<P>, dim3(c->nb_fluid), dim3(kBlock), 0, c->stream, A);
-  hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream, A.partials, c->nb_fluid, row);
+  hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream, static_cast<const double*>(A.partials),
+                     c->nb_fluid, row, 1, c->rows);
   HIP_TRY(c, hipGetLastError());
-  HIP_TRY(c, hipMemcpyAsync(out, row, 5 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  std::copy(c->rows, c->rows + 5, out);
   return LBM_OK;
 }
 
@@ -848,7 +858,7 @@ lbm_status check_adjoint_buffers(lbm_ctx* c, const void* state, const void* fiel
     default: return fn<kWideMode + LBM_BF16_DEV>((ctx), __VA_ARGS__);           \
   }
 
-lbm_status step_once(lbm_ctx* c, int slot, bool timed, void* fields) { DISPATCH(c, launch_step, slot, timed, fields); }
+lbm_status step_once(lbm_ctx* c, int slot, void* fields) { DISPATCH(c, launch_step, slot, fields); }
 lbm_status init_once(lbm_ctx* c, const uint8_t* solid, const uint8_t* react, const double* theta, double theta_uniform,
                      const double* rr, const double* rp, const double* c0) {
   DISPATCH(c, launch_init, solid, react, theta, theta_uniform, rr, rp, c0);
@@ -942,6 +952,13 @@ lbm_status lbm_init(const lbm_params* params, const uint8_t* solid, const double
   // disables that entry point, which reports it.
   c->static_scr = static_scratch(c->err, sizeof(c->err));
   c->err[0] = 0;
+  c->rows = nullptr;
+  if (hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&c->rows), 5 * sizeof(double) * kRing, hipHostMallocDefault);
+      e != hipSuccess) {
+    snprintf(g_err, sizeof(g_err), "hipHostMalloc: %s", hipGetErrorString(e));
+    delete c;
+    return LBM_ERR_HIP;
+  }
   // Stage the host inputs in the second state buffer (free until the first step).
   char* stage = c->ws + L.state[1];
   double* d_theta = reinterpret_cast<double*>(stage);
@@ -952,7 +969,7 @@ lbm_status lbm_init(const lbm_params* params, const uint8_t* solid, const double
   uint8_t* d_react = d_solid + N;
   auto bail = [&](lbm_status st) {
     snprintf(g_err, sizeof(g_err), "%s", c->err);
-    delete c;
+    lbm_free(c);
     return st;
   };
 #define INIT_TRY(expr)                                                                  \
@@ -983,19 +1000,16 @@ lbm_status lbm_init(const lbm_params* params, const uint8_t* solid, const double
 lbm_status lbm_step(lbm_ctx* c, int32_t nsteps, lbm_reductions* per_step) {
   if (!c) return LBM_ERR_ARG;
   if (nsteps < 0) return fail(c, LBM_ERR_ARG, "nsteps must be >= 0");
-  std::vector<double> rows;
   bool bad = false;
   int done = 0;
   while (done < nsteps) {
     const int chunk = std::min(kRing, nsteps - done);
     for (int t = 0; t < chunk; ++t) {
-      if (lbm_status s = step_once(c, t, true, nullptr); s != LBM_OK) return s;
+      if (lbm_status s = step_once(c, t, nullptr); s != LBM_OK) return s;
     }
     if (lbm_status s = launch_finish(c, chunk - 1); s != LBM_OK) return s;
-    rows.resize(5 * size_t(chunk));
-    HIP_TRY(c, hipMemcpyAsync(rows.data(), c->ws + c->L.ring, rows.size() * sizeof(double), hipMemcpyDeviceToHost,
-                              c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const double* rows = c->rows;
     if (c->prof) {
       for (int t = 0; t < chunk; ++t)
         for (int k = 0; k < kTimed; ++k) {
@@ -1026,7 +1040,7 @@ lbm_status lbm_step_async(lbm_ctx* c, int32_t nsteps) {
   if (!c) return LBM_ERR_ARG;
   if (nsteps < 0) return fail(c, LBM_ERR_ARG, "nsteps must be >= 0");
   for (int t = 0; t < nsteps; ++t) {
-    if (lbm_status s = step_once(c, t % kRing, false, nullptr); s != LBM_OK) return s;
+    if (lbm_status s = step_once(c, kNoSums, nullptr); s != LBM_OK) return s;
   }
   return LBM_OK;
 }
@@ -1041,7 +1055,7 @@ lbm_status lbm_fields_bytes(const lbm_params* params, size_t* bytes) {
 lbm_status lbm_step_fields(lbm_ctx* c, void* d_fields) {
   if (!c) return LBM_ERR_ARG;
   if (!d_fields) return fail(c, LBM_ERR_ARG, "a fields buffer is required");
-  return step_once(c, 0, false, d_fields);
+  return step_once(c, kNoSums, d_fields);
 }
 
 lbm_status lbm_step_from(lbm_ctx* c, const void* d_src, void* d_dst, void* d_fields) {
@@ -1212,6 +1226,7 @@ void lbm_free(lbm_ctx* c) {
   if (!c) return;
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
+  if (c->rows) (void)hipHostFree(c->rows);
   delete c;
 }
 

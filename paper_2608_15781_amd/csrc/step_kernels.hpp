@@ -150,9 +150,10 @@ __device__ inline void rn_densities(R q, R rm, R& rr, R& rp) {
 // Maps the hardware workgroup id to a logical tile so that each XCD (with its own L2) works on
 // one contiguous slab of the lattice; neighbouring rows then share that XCD's L2.
 // gridDim.x is always a multiple of kXcd.
-__device__ inline int logical_block() {
-  int per_xcd = gridDim.x / kXcd;
-  return (blockIdx.x % kXcd) * per_xcd + blockIdx.x / kXcd;
+// skip: leading workgroups without a tile (a multiple of kXcd).
+__device__ inline int logical_block(int skip = 0) {
+  const int per_xcd = (gridDim.x - skip) / kXcd, b = blockIdx.x - skip;
+  return (b % kXcd) * per_xcd + b / kXcd;
 }
 
 // The tile of kBlock consecutive fluid ids that this workgroup processes: its XCD-aware launch
@@ -160,8 +161,8 @@ __device__ inline int logical_block() {
 // launched in y-bands swept through z, so that tiles whose nodes neighbour each other across
 // planes are in flight on the same XCD and share its L2).
 template <class SA>
-__device__ inline int fluid_tile(const SA& A) {
-  const int lb = logical_block();
+__device__ inline int fluid_tile(const SA& A, int skip = 0) {
+  const int lb = logical_block(skip);
   return A.order ? A.order[lb] : lb;
 }
 
@@ -458,10 +459,8 @@ struct StepArgs {
   R* nraw;       // optional: per fluid id, the unit normal before the wetting realignment at
                  // wetting nodes (kept for the adjoint; elsewhere it equals n*)
   const R* wet;  // per fluid id 4-vector (n_s, cos(theta))
-  double* partials;
-  double* ring_row;  // 5 doubles of this step
-  // Deferred final reduction of the previous step, done by workgroup 0 of the step's first pass
-  // (null: none)
+  double* partials;  // per-workgroup sums of the step (null: none wanted)
+  // Deferred final reduction of the previous step, done by the step's first pass (null: none)
   const double* red_in;
   int red_n;
   double* red_out;
@@ -536,8 +535,54 @@ __device__ inline void pull_species(const StepArgs<P>& A, uint32_t t, uint32_t i
   }
 }
 
+// The wave's sums of four values per lane: lane l receives the sum of value l / 16. Two exchanges of
+// wave halves and rows (v_permlane32_swap, v_permlane16_swap: each leaves two half-summed values
+// in one register) and four rotations within rows of 16, 21 vector instructions and no LDS; five
+// separate butterflies took 60 LDS permutes and 30 additions, a third of the collide pass's tail.
+__device__ inline double from_words(uint32_t lo, uint32_t hi) {
+  return __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
+}
+__device__ inline void to_words(double v, uint32_t& lo, uint32_t& hi) {
+  const uint64_t b = uint64_t(__double_as_longlong(v));
+  lo = uint32_t(b);
+  hi = uint32_t(b >> 32);
+}
+// (a over both wave halves) in the lower lanes, (b over both) in the upper ones
+__device__ inline double fold_halves(double a, double b) {
+  uint32_t al, ah, bl, bh;
+  to_words(a, al, ah);
+  to_words(b, bl, bh);
+  const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+  return from_words(lo[0], hi[0]) + from_words(lo[1], hi[1]);
+}
+// (a over row pairs) in the even rows of 16 lanes, (b over row pairs) in the odd ones
+__device__ inline double fold_rows(double a, double b) {
+  uint32_t al, ah, bl, bh;
+  to_words(a, al, ah);
+  to_words(b, bl, bh);
+  const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+  return from_words(lo[0], hi[0]) + from_words(lo[1], hi[1]);
+}
+template <int K>  // the value of the lane K before in the row, rotating (DPP row_ror)
+__device__ inline double rotate_row(double v) {
+  uint32_t lo, hi;
+  to_words(v, lo, hi);
+  return from_words(uint32_t(__builtin_amdgcn_update_dpp(0, int(lo), 0x120 + K, 0xf, 0xf, true)),
+                    uint32_t(__builtin_amdgcn_update_dpp(0, int(hi), 0x120 + K, 0xf, 0xf, true)));
+}
+__device__ inline double wave_sums(double s0, double s1, double s2, double s3) {
+  double v = fold_rows(fold_halves(s0, s2), fold_halves(s1, s3));
+  v += rotate_row<8>(v);
+  v += rotate_row<4>(v);
+  v += rotate_row<2>(v);
+  v += rotate_row<1>(v);
+  return v;
+}
+
 // Sum of the per-workgroup partials (5 planes of nparts) by one workgroup of kBlock threads, in
-// a fixed order: strided per-thread sums, then wavefront shuffles, then the waves in order. Every
+// a fixed order: strided per-thread sums, then the wave's sums, then the waves in order. Every
 // caller uses this one routine with the same thread count, so a step's sums do not depend on
 // where the reduction ran.
 __device__ inline void reduce_partials(const double* partials, int nparts, double* out) {
@@ -555,29 +600,37 @@ __device__ inline void reduce_partials(const double* partials, int nparts, doubl
 #pragma unroll
     for (int j = 0; j < 5; ++j) t[j] += partials[size_t(j) * nparts + b];
   }
-#pragma unroll
-  for (int j = 0; j < 5; ++j) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) t[j] += __shfl_xor(t[j], off, 64);
-  }
+  const double v = wave_sums(t[0], t[1], t[2], t[3]), v4 = wave_sums(t[4], 0.0, 0.0, 0.0);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) red[wave][j] = t[j];
+  if (lane % 16 == 0) red[wave][lane / 16] = v;
+  if (lane == 0) red[wave][4] = v4;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 5) {
+    double sum = red[0][threadIdx.x];
 #pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      double v = red[0][j];
-#pragma unroll
-      for (int w = 1; w < kBlock / 64; ++w) v += red[w][j];
-      out[j] = v;
-    }
+    for (int w = 1; w < kBlock / 64; ++w) sum += red[w][threadIdx.x];
+    out[threadIdx.x] = sum;
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_finish_reduce(const double* partials, int nparts, double* out) {
-  reduce_partials(partials, nparts, out);
+// The sums of the last step of a chunk into its ring row, then rows 0 .. rows - 1 to host memory
+// (pinned: the kernel's own stores spare the copy and its wait, 8 of the 46 us of a one-step call).
+__global__ __launch_bounds__(kBlock) void k_finish_reduce(const double* partials, int nparts, double* ring, int rows,
+                                                          double* host) {
+  reduce_partials(partials, nparts, ring + 5 * (rows - 1));
+  __syncthreads();
+  if (host)
+    for (int i = threadIdx.x; i < 5 * rows; i += kBlock) host[i] = ring[i];
+}
+
+// A step's first kernel is launched with kXcd workgroups more when it also finishes the previous step's
+// sums (red_out): workgroup 0 does only that, the other seven return, so that no tile waits for the
+// sums, and the rest keep their XCD. True if the workgroup has no tile.
+template <class SA>
+__device__ inline bool finish_previous(const SA& A) {
+  if (!A.red_out || blockIdx.x >= kXcd) return false;
+  if (blockIdx.x == 0) reduce_partials(A.red_in, A.red_n, A.red_out);
+  return true;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -635,9 +688,9 @@ template <int P>
 __global__ __launch_bounds__(kBlock) void k_colour(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
-  if (A.red_out && blockIdx.x == 0) reduce_partials(A.red_in, A.red_n, A.red_out);
   using Off = typename Prec<P>::Off;
-  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
+  if (finish_previous(A)) return;
+  const uint32_t t = uint32_t(fluid_tile(A, A.red_out ? kXcd : 0)) * kBlock + threadIdx.x;
   if (t >= uint32_t(A.nfluid)) return;
   const ListNode ln = ldx<Off>(A.fluid, t);
   const int n = ln.node;
@@ -836,35 +889,24 @@ __device__ inline bool finite(R v) {
   return isfinite(v);
 }
 
-// Deterministic FP64 reduction of 5 sums over a workgroup of NT threads: wavefront shuffles, then
-// the workgroup's waves in fixed order; one partial per workgroup (plain stores, no fences or
-// atomics). The sums are finished by reduce_partials, after the grid, in workgroup order.
-template <int NT>
-__device__ inline void block_reduce5_n(double s[5], double* partials) {
-  __shared__ double red[NT / 64][5];
-#pragma unroll
-  for (int j = 0; j < 5; ++j) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s[j] += __shfl_xor(s[j], off, 64);
-  }
+// Deterministic FP64 reduction over the workgroup of four sums and of the lanes with s[4] != 0: the
+// wave's sums, then the workgroup's waves in fixed order; one partial per workgroup (plain stores, no
+// fences or atomics). The sums are finished by reduce_partials, after the grid, in workgroup order.
+__device__ inline void block_reduce5(const double s[5], double* partials, int skip = 0) {
+  __shared__ double red[kBlock / 64][5];
+  const double v = wave_sums(s[0], s[1], s[2], s[3]);
+  const int flagged = __popcll(__ballot(s[4] != 0));
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) red[wave][j] = s[j];
+  if (lane % 16 == 0) red[wave][lane / 16] = v;
+  if (lane == 0) red[wave][4] = double(flagged);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int lb = logical_block();
+  if (threadIdx.x < 5) {
+    double sum = red[0][threadIdx.x];
 #pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      double t = red[0][j];
-#pragma unroll
-      for (int w = 1; w < NT / 64; ++w) t += red[w][j];
-      partials[size_t(j) * gridDim.x + lb] = t;
-    }
+    for (int w = 1; w < kBlock / 64; ++w) sum += red[w][threadIdx.x];
+    partials[size_t(threadIdx.x) * (gridDim.x - skip) + logical_block(skip)] = sum;
   }
 }
-
-__device__ inline void block_reduce5(double s[5], double* partials) { block_reduce5_n<kBlock>(s, partials); }
 
 // H |G| at fluid node x: the curvature H = -(tr J - n.J.n) (eq. interface_curvature) with
 // J_ab = 3 sum_i w_i c_ib n*_a(x + c_i), times the gradient magnitude |G| of x; zero where
@@ -1062,8 +1104,9 @@ __global__ __launch_bounds__(kBlock) void k_collide(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
   using Off = typename Prec<P>::Off;
-  if (!IFACE && A.red_out && blockIdx.x == 0) reduce_partials(A.red_in, A.red_n, A.red_out);
-  const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;
+  if (!IFACE && finish_previous(A)) return;
+  const int skip = !IFACE && A.red_out ? kXcd : 0;
+  const uint32_t t = uint32_t(fluid_tile(A, skip)) * kBlock + threadIdx.x;
   double red5[5] = {0, 0, 0, 0, 0};
   if (t < uint32_t(A.nfluid)) {
     const ListNode ln = ldx<Off>(A.fluid, t);
@@ -1114,7 +1157,19 @@ __global__ __launch_bounds__(kBlock) void k_collide(StepArgs<P> A) {
     }
     collide_node<P, MOM>(A, t, n, inf, f, g, rn, cur, red5);
   }
-  if (!MOM) block_reduce5(red5, A.partials);
+  if (!MOM && A.partials) block_reduce5(red5, A.partials, skip);
+}
+
+// Zero at the solid nodes of the fields of lbm_moments (any may be null).
+template <class R>
+__global__ __launch_bounds__(kBlock) void k_clear_solids(const uint32_t* info, int N, R* rr, R* rp, R* rn, R* u, R* c) {
+  const size_t n = size_t(blockIdx.x) * kBlock + threadIdx.x, count = size_t(N);
+  if (n >= count || (info[n] & kFluid)) return;
+  if (rr) rr[n] = R(0);
+  if (rp) rp[n] = R(0);
+  if (rn) rn[n] = R(0);
+  if (u) u[n] = u[count + n] = u[2 * count + n] = R(0);
+  if (c) c[n] = R(0);
 }
 
 // ---------------------------------------------------------------------------------------------
