@@ -187,8 +187,11 @@ __global__ __launch_bounds__(kBlock) void k_adj_seed(StepArgs<P> A, typename Pre
 // ---------------------------------------------------------------------------------------------
 // Reverse of the collide kernel at one fluid node (forward arithmetic recomputed as in k_collide).
 // Register budget: the pull sources and the species populations, needed again only at the end,
-// wait in LDS (25 KB per workgroup in FP32), which brings the FP32/FP16/BF16 kernels to 165
-// VGPRs and three waves per SIMD (requested below) without spills; FP64 keeps one wave.
+// wait in LDS (25 KB per workgroup in FP32), and every plane is addressed by a uniform base and
+// a 32-bit offset, which brings the FP32 kernel to 119 VGPRs (165 with 64-bit addresses) and
+// four waves per SIMD without spills (three are requested below); FP64 keeps one wave. Bound by
+// the latency of its dependent rounds of loads (ids, normals, adjoint planes) at that occupancy:
+// asking for all adjoint planes with the first round needs 131 VGPRs and cost 0.9% of the pass.
 // ---------------------------------------------------------------------------------------------
 template <int P>
 __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
@@ -199,6 +202,7 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
   double gxi = 0.0;
   if (t < uint32_t(A.nfluid)) {
     const ListNode ln = ldx<Off>(A.fluid, t);
+    const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
     const int n = ln.node;
     const uint32_t inf = ln.info;
     const Nbr nb = make_nbr(n, inf, A.geo);
@@ -230,8 +234,7 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
     const R irm = R(1) / rm;
     const R ux = mx * irm, uy = my * irm, uz = mz * irm;
     R rr, rp;
-    rn_densities(A.rhoN[n], rm, rr, rp);
-    const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
+    rn_densities(ldx<Off>(A.rhoN, uint32_t(n)), rm, rr, rp);
     const R nn[3] = {nsv.x, nsv.y, nsv.z};
     const R glen = nsv.w;
     const bool has_n = glen > A.eps;
@@ -312,11 +315,12 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
     const R vc = keep * A.beta * rr * rp * irm;
 
     // ---------------- reverse ----------------
+    const auto lin = [&](int plane) { return ldx<Off>(J.lin + size_t(plane) * A.ps, t); };
     R lf[19];
 #pragma unroll
-    for (int i = 0; i < 19; ++i) lf[i] = J.lin[size_t(i) * A.ps + t];
-    const R la = J.lin[size_t(kAdjA) * A.ps + t];
-    const R lv[3] = {J.lin[size_t(kAdjV) * A.ps + t], J.lin[size_t(kAdjV + 1) * A.ps + t], J.lin[size_t(kAdjV + 2) * A.ps + t]};
+    for (int i = 0; i < 19; ++i) lf[i] = lin(i);
+    const R la = lin(kAdjA);
+    const R lv[3] = {lin(kAdjV), lin(kAdjV + 1), lin(kAdjV + 2)};
     R l_C = 0, l_delta = 0, l_up[3] = {0, 0, 0};
     R l_g[7] = {0, 0, 0, 0, 0, 0, 0};
     if (A.species) {
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
         const R geq = wc * C * (R(1) + R(4) * cu);
         const R gi = inlet ? geq : g[i];
         const R pre = gi + (geq - gi) * A.inv_tau_c;
-        const R lgo = J.lin[size_t(kAdjG + i) * A.ps + t];
+        const R lgo = lin(kAdjG + i);
         const R l_pre = lgo * sink;
         l_sink += lgo * pre;
         R l_geq = l_pre * A.inv_tau_c;
@@ -495,25 +499,23 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
       if (cx && cz) v += R(cx * cz) * l_pxz;
       if (cy && cz) v += R(cy * cz) * l_pyz;
       // transpose of the pull: the population S_q(src) read by this node as direction i
-      const bool bb = (i < 18) && ((inf >> i) & 1u);
-      const int src = (i < 18) ? sid[i] : t;
-      const int q = bb ? D::opp[i] : i;
-      J.lout[size_t(q) * A.ps + src] = v;
+      if (i < 18)
+        ref_pull<Off>(J.lout, A.ps, i, D::opp[i], sid[i < 18 ? i : 0], inf) = v;
+      else
+        refx<Off>(J.lout + 18 * A.ps, t) = v;
     }
     if (A.species) {
+      R* lg = J.lout + size_t(kAdjG) * A.ps;
 #pragma unroll
       for (int i = 0; i < 6; ++i) {
-        if (i == 1 && outlet) {
-          J.lgo[n] = l_g[1];
-        } else {
-          const bool bb = (inf >> i) & 1u;
-          const int q = bb ? D3Q7::opp[i] : i;
-          J.lout[size_t(kAdjG + q) * A.ps + sid[i]] = l_g[i];
-        }
+        if (i == 1 && outlet)
+          refx<Off>(J.lgo, uint32_t(n)) = l_g[1];
+        else
+          ref_pull<Off>(lg, A.ps, i, D3Q7::opp[i], sid[i], inf) = l_g[i];
       }
-      J.lout[size_t(kAdjG + 6) * A.ps + t] = l_g[6];
+      refx<Off>(lg + 6 * A.ps, t) = l_g[6];
     }
-    J.lrn[n] = l_rn;
+    refx<Off>(J.lrn, uint32_t(n)) = l_rn;
     st4<Off>(J.lng, t, l_n[0], l_n[1], l_n[2], l_glen);
     st4<Off>(J.lHn, t, has_n ? l_H : R(0), nn[0], nn[1], nn[2]);
   }
@@ -604,9 +606,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_normal(StepArgs<P> A, AdjArgs<ty
 #pragma unroll
     for (int a = 0; a < 3; ++a) lG[a] = (ln[a] - lnn * nv[a]) * il + lgl * nv[a];
   }
-  J.lG[n] = lG[0];
-  J.lG[N + n] = lG[1];
-  J.lG[2 * N + n] = lG[2];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) refx<Off>(J.lG + a * N, uint32_t(n)) = lG[a];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -630,11 +631,10 @@ __device__ inline typename Prec<P>::R grad_transpose(const StepArgs<P>& A, const
 #pragma unroll
     for (int i = 0; i < 18; ++i) {
       // solid y: bit opp(i) set means y - c_i is fluid
-      const bool src_fluid = (inf >> D::opp[i]) & 1u;
-      const int m = src_fluid ? nb.at(-D::cx[i], -D::cy[i], -D::cz[i]) : n;
-      gx[i] = D::cx[i] ? J.lG[m] : R(0);
-      gy[i] = D::cy[i] ? J.lG[N + m] : R(0);
-      gz[i] = D::cz[i] ? J.lG[2 * N + m] : R(0);
+      const uint32_t m = uint32_t(((inf >> D::opp[i]) & 1u) ? nb.at(-D::cx[i], -D::cy[i], -D::cz[i]) : n);
+      gx[i] = D::cx[i] ? ldx<Off>(J.lG, m) : R(0);
+      gy[i] = D::cy[i] ? ldx<Off>(J.lG + N, m) : R(0);
+      gz[i] = D::cz[i] ? ldx<Off>(J.lG + 2 * N, m) : R(0);
     }
   } else {
     // Fluid y (bit i set: y - c_i is solid, read as y and discarded): each component plane with
@@ -685,13 +685,15 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad_ext(StepArgs<P> A, AdjArgs<
   R den = 0;  // > 0: a solid node on this list has a fluid neighbour
 #pragma unroll
   for (int k = 0; k < 18; ++k) den = ((inf >> k) & 1u) ? den + R(D::w(k)) : den;
-  J.lrn[n] = s / den;
+  refx<Off>(J.lrn, uint32_t(n)) = s / den;
 }
 
 // ---------------------------------------------------------------------------------------------
 // Transpose of the extrapolation rho^N(y) = sum_j w_j rho^N(y + c_j) / den(y) into the fluid node
 // z = y + c_j, then rho^N = (2 rho^r - rho^m)/rho^m reversed to d/d rho^r and d/d rho^m (the
 // colour pass forms rho^N from rho^r and rho^p = rho^m - rho^r separately; the same function).
+// Bound by the cache requests of its gathers: the loads at solid neighbours are masked, so that
+// the lanes with a fluid one request nothing (96^3 FP32: 15.9 -> 14.3 us).
 // ---------------------------------------------------------------------------------------------
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_adj_colour(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
@@ -705,21 +707,24 @@ __global__ __launch_bounds__(kBlock) void k_adj_colour(StepArgs<P> A, AdjArgs<ty
   const uint32_t inf = ln.info;
   const Nbr nb = make_nbr(n, inf, A.geo);
   // At a solid y the adjoint is stored already divided by den(y) (k_adj_grad_ext). Loads for all
-  // directions first (a fluid z - c_j reads this node's own entry, discarded).
+  // directions first (none for a fluid z - c_j).
   R ly[18];
 #pragma unroll
-  for (int j = 0; j < 18; ++j) ly[j] = J.lrn[((inf >> j) & 1u) ? nb.at(-D::cx[j], -D::cy[j], -D::cz[j]) : n];
+  for (int j = 0; j < 18; ++j) {
+    ly[j] = R(0);
+    if ((inf >> j) & 1u) ly[j] = ldx<Off>(J.lrn, uint32_t(nb.at(-D::cx[j], -D::cy[j], -D::cz[j])));
+  }
   // d/d rho^N of this fluid node: the collide part plus the gradient stencil's transpose
-  R l = J.lrn[n] + grad_transpose<P, false>(A, J, n, inf, nb);
+  R l = ldx<Off>(J.lrn, uint32_t(n)) + grad_transpose<P, false>(A, J, n, inf, nb);
 #pragma unroll
   for (int j = 0; j < 18; ++j) l = ((inf >> j) & 1u) ? l + R(D::w(j)) * ly[j] : l;  // z - c_j is solid
-  const R rm = J.rmv[n];
-  const R q = A.rhoN[n];
+  const R rm = ldx<Off>(J.rmv, uint32_t(n));
+  const R q = ldx<Off>(A.rhoN, uint32_t(n));
   const R one_plus_rn = signbit(q) ? R(2) + q : q;  // 1 + rho^N = 2 rho^r / rho^m
   typename V2<R>::T v;
   v.x = R(2) * l / rm;
   v.y = -one_plus_rn * l / rm;
-  reinterpret_cast<typename V2<R>::T*>(J.lr2)[n] = v;
+  refx<Off>(reinterpret_cast<typename V2<R>::T*>(J.lr2), uint32_t(n)) = v;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -745,7 +750,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_final(StepArgs<P> A, AdjArgs<typ
   // itself (bounce-back), and y for the rest population.
   using V2R = typename V2<R>::T;
   const V2R* lr2 = reinterpret_cast<const V2R*>(J.lr2);
-  const V2R own2 = lr2[n];
+  const V2R own2 = ldx<Off>(lr2, uint32_t(n));
   V2R rdv[18];
   row_shared<true>(inf, own2,
                    [&](int i) { return uint32_t(((inf >> i) & 1u) ? n : nb.at(-D::cx[i], -D::cy[i], -D::cz[i])); },
@@ -754,25 +759,25 @@ __global__ __launch_bounds__(kBlock) void k_adj_final(StepArgs<P> A, AdjArgs<typ
   for (int q = 0; q < 19; ++q) {
     const V2R lv2 = (q == 18) ? own2 : rdv[D::opp[q]];
     const R lr = lv2.x, lm = lv2.y;
-    const R fq = Prec<P>::ld(A.fin[size_t(q) * A.ps + t], R(D::w(q)), A.inv_scale);
-    J.lout[size_t(q) * A.ps + t] += lr * a + lm;
+    const R fq = Prec<P>::ld(ldx<Off>(A.fin + size_t(q) * A.ps, t), R(D::w(q)), A.inv_scale);
+    refx<Off>(J.lout + size_t(q) * A.ps, t) += lr * a + lm;
     la += lr * fq;
     const R wl = R(D::w_over_len(q)) * lr;
     lv[0] += wl * R(D::cx[q]);
     lv[1] += wl * R(D::cy[q]);
     lv[2] += wl * R(D::cz[q]);
   }
-  J.lout[size_t(kAdjA) * A.ps + t] = la;
-  J.lout[size_t(kAdjV) * A.ps + t] = lv[0];
-  J.lout[size_t(kAdjV + 1) * A.ps + t] = lv[1];
-  J.lout[size_t(kAdjV + 2) * A.ps + t] = lv[2];
-  if (A.species && (inf & kOutlet)) J.lout[size_t(kAdjG + 1) * A.ps + t] += J.lgo[n];
+  refx<Off>(J.lout + size_t(kAdjA) * A.ps, t) = la;
+  refx<Off>(J.lout + size_t(kAdjV) * A.ps, t) = lv[0];
+  refx<Off>(J.lout + size_t(kAdjV + 1) * A.ps, t) = lv[1];
+  refx<Off>(J.lout + size_t(kAdjV + 2) * A.ps, t) = lv[2];
+  if (A.species && (inf & kOutlet)) refx<Off>(J.lout + size_t(kAdjG + 1) * A.ps, t) += J.lgo[n];
   // Species populations without a reader, which the scatter of k_adj_collide left untouched:
   // their adjoint is zero. An outflow node takes its own S_1 instead of the one from its periodic
   // +x image, so S_1 of an inlet node whose -x image is an outflow node is unread, and S_0 of an
   // outflow node whose +x image is solid is unread (bounce-back would have read it).
-  if (A.species && (inf & kInlet) && !(inf & 1u)) J.lout[size_t(kAdjG + 1) * A.ps + t] = R(0);
-  if (A.species && (inf & kOutlet) && (inf & 2u)) J.lout[size_t(kAdjG + 0) * A.ps + t] = R(0);
+  if (A.species && (inf & kInlet) && !(inf & 1u)) refx<Off>(J.lout + size_t(kAdjG + 1) * A.ps, t) = R(0);
+  if (A.species && (inf & kOutlet) && (inf & 2u)) refx<Off>(J.lout + size_t(kAdjG + 0) * A.ps, t) = R(0);
 }
 
 

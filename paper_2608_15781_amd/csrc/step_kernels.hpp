@@ -500,10 +500,14 @@ __device__ inline typename Prec<P>::R ld_species(const StepArgs<P>& A, int q, ty
 // of the opposite direction where bit i of inf is set (bounce-back; src is then the node itself).
 // The two planes share one uniform base, that of the lower one, and the select adds their distance.
 template <class Off, class S>
-__device__ inline S ld_pull(const S* planes, size_t ps, int i, int opp, uint32_t src, uint32_t inf) {
+__device__ inline S& ref_pull(S* planes, size_t ps, int i, int opp, uint32_t src, uint32_t inf) {
   const int lo = i < opp ? i : opp, dist = i < opp ? opp - i : i - opp;
   const uint32_t upper = bit_mask(i < opp ? inf : ~inf, i);
-  return ldx<Off>(planes + size_t(lo) * ps, Off(src) + (Off(int64_t(int32_t(upper))) & Off(size_t(dist) * ps)));
+  return refx<Off>(planes + size_t(lo) * ps, Off(src) + (Off(int64_t(int32_t(upper))) & Off(size_t(dist) * ps)));
+}
+template <class Off, class S>
+__device__ inline S ld_pull(const S* planes, size_t ps, int i, int opp, uint32_t src, uint32_t inf) {
+  return ref_pull<Off>(const_cast<S*>(planes), ps, i, opp, src, inf);
 }
 
 // Pull of fluid node t with halfway bounce-back: f^m_i from S_t at x - c_i, or S_t,opp(i) at x
