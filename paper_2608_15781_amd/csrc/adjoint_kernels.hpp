@@ -202,7 +202,8 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
   double gxi = 0.0;
   if (t < uint32_t(A.nfluid)) {
     const ListNode ln = ldx<Off>(A.fluid, t);
-    const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
+    const Vec3<R> nsv = ld3<Off>(A.nst, t);
+    const R glen = ldx<Off>(A.glen, t);
     const int n = ln.node;
     const uint32_t inf = ln.info;
     const Nbr nb = make_nbr(n, inf, A.geo);
@@ -236,7 +237,6 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
     R rr, rp;
     rn_densities(ldx<Off>(A.rhoN, uint32_t(n)), rm, rr, rp);
     const R nn[3] = {nsv.x, nsv.y, nsv.z};
-    const R glen = nsv.w;
     const bool has_n = glen > A.eps;
     R H = 0;
     R Js[3] = {0, 0, 0};  // sum_b n*_b (J_ab + J_ba), the only part of J the reverse needs
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
       R Jm[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
 #pragma unroll
       for (int i = 0; i < 18; ++i) {
-        const typename V4<R>::T mv = ld4<Off>(A.nst, sid[D::opp[i]]);  // own id where x + c_i is solid
+        const Vec3<R> mv = ld3<Off>(A.nst, sid[D::opp[i]]);  // own id where x + c_i is solid
         const R a0 = mv.x, a1 = mv.y, a2 = mv.z;
         const R w3 = R(3.0 * D::w(i));
         if (D::cx[i]) { Jm[0][0] += w3 * R(D::cx[i]) * a0; Jm[1][0] += w3 * R(D::cx[i]) * a1; Jm[2][0] += w3 * R(D::cx[i]) * a2; }
@@ -547,7 +547,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_normal(StepArgs<P> A, AdjArgs<ty
   // share one memory round trip with the neighbours' ids (the wetting entries are read at every
   // node and used only at wetting nodes): the forward normal pass's n* and |G|, the normal
   // before realignment, the wetting data, dL/dn* and dL/d|G|, and the running dL/dtheta.
-  const typename V4<R>::T nsv = ld4<Off>(A.nst, t);
+  const Vec3<R> nsv = ld3<Off>(A.nst, t);
+  const R len = ldx<Off>(A.glen, t);
   const typename V4<R>::T rv = ld4<Off>(A.nraw, t);
   const typename V4<R>::T wv = ld4<Off>(A.wet, t);
   const typename V4<R>::T lgv = ld4<Off>(J.lng, t);
@@ -573,7 +574,6 @@ __global__ __launch_bounds__(kBlock) void k_adj_normal(StepArgs<P> A, AdjArgs<ty
   }
   // The unit normal of this node: n* unless the wetting realignment changed it, in which case
   // the normal pass kept the one before realignment.
-  const R len = nsv.w;
   R lG[3] = {0, 0, 0};
   if (len > A.eps) {
     const R il = R(1) / len;

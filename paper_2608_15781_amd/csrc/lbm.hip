@@ -39,7 +39,7 @@ size_t store_bytes(int precision) { return precision == LBM_FP64 ? 8 : (precisio
 size_t real_bytes(int precision) { return precision == LBM_FP64 ? 8 : 4; }
 
 struct Layout {
-  size_t info, wet, rhoN, nst, state[2], partials, ring, lists[2], ids, counts, order, total;
+  size_t info, wet, rhoN, nst, glen, state[2], partials, ring, lists[2], ids, counts, order, total;
   size_t f_off, a_off, g_off, c_off, state_bytes;  // within one state buffer
   size_t ps;  // elements between consecutive state (and adjoint) planes
   int nblocks;  // one thread per node, rounded up to a multiple of kXcd workgroups
@@ -108,7 +108,8 @@ Layout make_layout(const lbm_params& p) {
   L.info = o; o = align_up(o + 4 * N);      // per node
   L.wet = o; o = align_up(o + 4 * r * F);   // per fluid id
   L.rhoN = o; o = align_up(o + r * N);      // per node (read at solid nodes too)
-  L.nst = o; o = align_up(o + 4 * r * F);   // per fluid id
+  L.nst = o; o = align_up(o + 3 * r * F);   // per fluid id
+  L.glen = o; o = align_up(o + r * F);      // per fluid id
   L.partials = o; o = align_up(o + 2 * 5 * sizeof(double) * size_t(nb));  // two sets, used in turn
   L.ring = o; o = align_up(o + 5 * sizeof(double) * kRing);
   L.lists[0] = o; o = align_up(o + sizeof(ListNode) * F);  // fluid nodes
@@ -133,7 +134,7 @@ struct AdjLayout {
 // n* and |G| (per fluid id), the normal before realignment at wetting nodes (per fluid id),
 // rho^m (dense).
 struct FieldLayout {
-  size_t rhoN, nst, nraw, rm, total;
+  size_t rhoN, nst, glen, nraw, rm, total;
 };
 
 FieldLayout make_field_layout(const lbm_params& p) {
@@ -142,7 +143,8 @@ FieldLayout make_field_layout(const lbm_params& p) {
   const size_t r = real_bytes(p.precision);
   size_t o = 0;
   F.rhoN = o; o = align_up(o + r * N);
-  F.nst = o; o = align_up(o + 4 * r * fluid_bound(p));
+  F.nst = o; o = align_up(o + 3 * r * fluid_bound(p));
+  F.glen = o; o = align_up(o + r * fluid_bound(p));
   F.nraw = o; o = align_up(o + 4 * r * fluid_bound(p));
   F.rm = o; o = align_up(o + r * N);
   F.total = o;
@@ -496,6 +498,7 @@ StepArgs<P> make_args(lbm_ctx* c, int src_buf) {
   A.cout = reinterpret_cast<R*>(db + L.c_off);
   A.rhoN = reinterpret_cast<R*>(c->ws + L.rhoN);
   A.nst = reinterpret_cast<R*>(c->ws + L.nst);
+  A.glen = reinterpret_cast<R*>(c->ws + L.glen);
   A.wet = reinterpret_cast<const R*>(c->ws + L.wet);
   A.partials = reinterpret_cast<double*>(c->ws + L.partials);
   A.relax = R(1.0 - 1.0 / p.tau);
@@ -520,6 +523,7 @@ void use_fields(lbm_ctx* c, StepArgs<P>& A, void* fields) {
   char* fb = static_cast<char*>(fields);
   A.rhoN = reinterpret_cast<R*>(fb + FL.rhoN);
   A.nst = reinterpret_cast<R*>(fb + FL.nst);
+  A.glen = reinterpret_cast<R*>(fb + FL.glen);
   A.nraw = reinterpret_cast<R*>(fb + FL.nraw);
   A.rm_out = reinterpret_cast<R*>(fb + FL.rm);
 }
