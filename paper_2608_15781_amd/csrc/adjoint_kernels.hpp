@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs
     st4<Off>(J.lHn, t, has_n ? l_H : R(0), nn[0], nn[1], nn[2]);
   }
   double s5[5] = {gxi, 0, 0, 0, 0};
-  block_reduce5(s5, J.partials);
+  block_reduce5<kBlock>(s5, J.partials);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_normal(StepArgs<P> A, AdjArgs<ty
   using D = D3Q19;
   // Workgroup 0 first finishes the xi sum of k_adj_collide and adds it to dL/dxi.
   if (blockIdx.x == 0) {
-    reduce_partials(J.partials, J.nparts, J.sum);
+    reduce_partials<kBlock>(J.partials, J.nparts, J.sum);
     if (threadIdx.x == 0) *J.gxi += J.sum[0];
   }
   const uint32_t t = uint32_t(fluid_tile(A)) * kBlock + threadIdx.x;

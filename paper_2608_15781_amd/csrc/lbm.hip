@@ -38,6 +38,26 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 size_t store_bytes(int precision) { return precision == LBM_FP64 ? 8 : (precision == LBM_FP32 ? 4 : 2); }
 size_t real_bytes(int precision) { return precision == LBM_FP64 ? 8 : 4; }
 
+// The colour and collide passes share each tile of kBlock nodes among 2^split workgroups. Two of 128
+// threads where that puts more compute units to work or ends the launch more evenly, by the waves of
+// fluid nodes per compute unit (256 of them, four SIMDs each); microseconds per step unsplit and
+// split, porous cubes:
+//   up to two, each unit gets one wave pair instead of every second unit two: 16^3 FP64 18.5 -> 16.8,
+//     FP32 16.1 -> 15.1; 40^3 FP64 20.1 -> 18.4, FP32 17.4 -> 16.3
+//   up to four, one unsplit workgroup per unit has a wave on each SIMD, two split ones may share two
+//     of them: 48^3 FP64 21.5 -> 23.0, FP32 17.8 -> 18.7, so unsplit
+//   up to twelve: 56^3 FP64 28.2 -> 26.8, FP32 22.3 -> 21.1; 64^3 FP64 36.0 -> 34.4, FP32 25.7 -> 24.7
+//   beyond, FP32 and the 2-byte storages are even (80^3 31.8 and 32.0) or lose (512 x 512 x 128 1932 -> 1941), and FP64,
+//     of whose collide workgroups only two fit a unit, gains (128^3 239 -> 230).
+// Workgroups of 64 threads are as fast as those of 128 up to 32^3 and cost the sums 2 us more.
+int pull_split(const lbm_params& p, int nfluid) {
+  constexpr int kPerUnit = 256 * 64;  // nodes of one wave per compute unit
+  if (nfluid <= 2 * kPerUnit) return 1;
+  if (nfluid <= 4 * kPerUnit) return 0;
+  return p.precision == LBM_FP64 || nfluid <= 12 * kPerUnit ? 1 : 0;
+}
+constexpr int kMostSplit = 1;
+
 struct Layout {
   size_t info, wet, rhoN, nst, glen, state[2], partials, ring, lists[2], ids, counts, order, total;
   size_t f_off, a_off, g_off, c_off, state_bytes;  // within one state buffer
@@ -110,7 +130,7 @@ Layout make_layout(const lbm_params& p) {
   L.rhoN = o; o = align_up(o + r * N);      // per node (read at solid nodes too)
   L.nst = o; o = align_up(o + 3 * r * F);   // per fluid id
   L.glen = o; o = align_up(o + r * F);      // per fluid id
-  L.partials = o; o = align_up(o + 2 * 5 * sizeof(double) * size_t(nb));  // two sets, used in turn
+  L.partials = o; o = align_up(o + 2 * 5 * sizeof(double) * (size_t(nb) << kMostSplit));  // two sets, used in turn
   L.ring = o; o = align_up(o + 5 * sizeof(double) * kRing);
   L.lists[0] = o; o = align_up(o + sizeof(ListNode) * F);  // fluid nodes
   L.lists[1] = o; o = align_up(o + sizeof(ListNode) * E);  // solid nodes with extrapolated colour
@@ -183,6 +203,7 @@ struct lbm_ctx {
   int cur;  // index of the state buffer holding S_t
   int64_t steps;
   int nfluid, next;      // list lengths
+  int split, nb_pull;  // workgroups of the colour and collide passes: nb_fluid tiles, each shared by 2^split
   int nb_fluid, nb_ext;  // workgroups over each list (multiples of kXcd, 0 if empty)
   bool ordered;          // fluid-list tiles launched in the order stored at L.order
   double* rows;          // pinned host memory: the ring rows of a chunk, written by k_finish_reduce
@@ -533,15 +554,33 @@ void use_fields(lbm_ctx* c, StepArgs<P>& A, void* fields) {
 // collide kernel is the whole step, and the other passes run only for `fields`. Measured on the
 // 128^3 porous mask, one colour, FP64: 217 us a step with the four passes, 120 us with one (colour 67,
 // extrapolation 10, normals 23 and collide 109 us; the fused kernel pulls f^m once).
+// The colour pass, and the collide pass of a step, over the tiles in workgroups of kBlock >> c->split
+// threads; `first`: the step's first pass, which also finishes the previous step's sums.
+template <int P>
+void launch_colour(lbm_ctx* c, const StepArgs<P>& A, bool first = false) {
+  const dim3 grid(c->nb_pull + (first && A.red_out ? kXcd : 0));
+  if (c->split)
+    hipLaunchKernelGGL((k_colour<P, kBlock / 2>), grid, dim3(kBlock / 2), 0, c->stream, A);
+  else
+    hipLaunchKernelGGL((k_colour<P, kBlock>), grid, dim3(kBlock), 0, c->stream, A);
+}
+template <int P, bool IFACE>
+void launch_collide(lbm_ctx* c, const StepArgs<P>& A) {
+  const dim3 grid(c->nb_pull + (!IFACE && A.red_out ? kXcd : 0));
+  if (c->split)
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock / 2>), grid, dim3(kBlock / 2), 0, c->stream, A);
+  else
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock>), grid, dim3(kBlock), 0, c->stream, A);
+}
+
 template <int P>
 lbm_status enqueue_step(lbm_ctx* c, const StepArgs<P>& A, hipEvent_t* ev, bool fields, bool collide = true) {
   const dim3 block(kBlock), gf(c->nb_fluid), ge(c->nb_ext);
   const bool iface = uses_normals(c->p);
-  const dim3 gfirst(c->nb_fluid + (A.red_out ? kXcd : 0));  // of the pass that finishes the previous sums
   StepArgs<P> AC = A;
   if (!iface) AC.red_out = nullptr;
   if (ev) HIP_TRY(c, hipEventRecord(ev[0], c->stream));
-  if ((iface || fields) && c->nb_fluid) hipLaunchKernelGGL(k_colour<P>, iface ? gfirst : gf, block, 0, c->stream, AC);
+  if ((iface || fields) && c->nb_fluid) launch_colour<P>(c, AC, iface);
   if (ev) HIP_TRY(c, hipEventRecord(ev[1], c->stream));
   if ((iface || fields) && c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
   if (ev) HIP_TRY(c, hipEventRecord(ev[2], c->stream));
@@ -549,9 +588,9 @@ lbm_status enqueue_step(lbm_ctx* c, const StepArgs<P>& A, hipEvent_t* ev, bool f
   if (ev) HIP_TRY(c, hipEventRecord(ev[3], c->stream));
   if (collide && c->nb_fluid) {
     if (iface)
-      hipLaunchKernelGGL((k_collide<P, false, true>), gf, block, 0, c->stream, A);
+      launch_collide<P, true>(c, A);
     else
-      hipLaunchKernelGGL((k_collide<P, false, false>), gfirst, block, 0, c->stream, A);
+      launch_collide<P, false>(c, A);
   }
   if (ev) HIP_TRY(c, hipEventRecord(ev[4], c->stream));
   HIP_TRY(c, hipGetLastError());
@@ -564,7 +603,7 @@ constexpr int kNoSums = -1;
 // The partial sums of the step in ring row `slot`. Two sets are used in turn, so that a step's
 // first workgroup can sum the previous step's set while the others write this step's.
 double* step_partials(lbm_ctx* c, int slot) {
-  return reinterpret_cast<double*>(c->ws + c->L.partials) + (slot & 1) * 5 * size_t(c->nb_fluid);
+  return reinterpret_cast<double*>(c->ws + c->L.partials) + (slot & 1) * 5 * size_t(c->nb_pull);
 }
 
 template <int P>
@@ -579,7 +618,7 @@ lbm_status launch_step(lbm_ctx* c, int slot, void* fields) {
     double* ring = reinterpret_cast<double*>(c->ws + c->L.ring);
     A.partials = step_partials(c, slot);
     A.red_in = step_partials(c, slot + 1);
-    A.red_n = c->nb_fluid;
+    A.red_n = c->nb_pull;
     A.red_out = slot > 0 ? ring + 5 * size_t(slot - 1) : nullptr;
     if (A.red_out && !c->nb_fluid)
       hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream, A.red_in, A.red_n, ring, slot,
@@ -619,7 +658,7 @@ lbm_status launch_step_from(lbm_ctx* c, const void* src, void* dst, void* fields
 lbm_status launch_finish(lbm_ctx* c, int slot) {
   double* ring = reinterpret_cast<double*>(c->ws + c->L.ring);
   hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream,
-                     static_cast<const double*>(step_partials(c, slot)), c->nb_fluid, ring, slot + 1, c->rows);
+                     static_cast<const double*>(step_partials(c, slot)), c->nb_pull, ring, slot + 1, c->rows);
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
 }
@@ -634,12 +673,12 @@ lbm_status launch_moments(lbm_ctx* c, void* rr, void* rp, void* rn, void* u, voi
   hipLaunchKernelGGL(k_clear_solids<R>, dim3((c->N + kBlock - 1) / kBlock), block, 0, c->stream, A.info, c->N, A.m_rr,
                      A.m_rp, A.m_rn, A.m_u, A.m_c);
   if (!uses_normals(c->p)) {
-    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false>), gf, block, 0, c->stream, A);
+    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false, kBlock>), gf, block, 0, c->stream, A);
   } else {
-    if (c->nb_fluid) hipLaunchKernelGGL(k_colour<P>, gf, block, 0, c->stream, A);
+    if (c->nb_fluid) launch_colour<P>(c, A);
     if (c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
     if (c->nb_fluid) hipLaunchKernelGGL(k_normal<P>, gf, block, 0, c->stream, A);
-    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, true>), gf, block, 0, c->stream, A);
+    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, true, kBlock>), gf, block, 0, c->stream, A);
   }
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
@@ -732,6 +771,8 @@ lbm_status launch_init(lbm_ctx* c, const uint8_t* d_solid, const uint8_t* d_reac
                      reinterpret_cast<R*>(c->ws + c->L.wet));
   c->nb_fluid = rounded_blocks(c->nfluid);
   c->nb_ext = rounded_blocks(c->next);
+  c->split = pull_split(p, c->nfluid);
+  c->nb_pull = c->nb_fluid << c->split;
   if (lbm_status s = build_tile_order(c); s != LBM_OK) return s;
   // The initial state goes into buffer 0 (make_args with src 1 writes buffer 0).
   StepArgs<P> A = make_args<P>(c, 1);
@@ -816,7 +857,7 @@ lbm_status launch_adj_step(lbm_ctx* c, const void* state, const void* fields, co
   const dim3 gf(c->nb_fluid), ge(c->nb_ext), block(kBlock);
   // Forward fields of level t.
   if (!fields) {
-    if (c->nb_fluid) hipLaunchKernelGGL(k_colour<P>, gf, block, 0, c->stream, A);
+    if (c->nb_fluid) launch_colour<P>(c, A);
     if (c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
     if (c->nb_fluid) hipLaunchKernelGGL(k_normal<P>, gf, block, 0, c->stream, A);
   }

@@ -177,9 +177,16 @@ __device__ inline int logical_block(int skip = 0) {
 // launched in y-bands swept through z, so that tiles whose nodes neighbour each other across
 // planes are in flight on the same XCD and share its L2).
 template <class SA>
-__device__ inline int fluid_tile(const SA& A, int skip = 0) {
-  const int lb = logical_block(skip);
+__device__ inline int fluid_tile(const SA& A) {
+  const int lb = logical_block();
   return A.order ? A.order[lb] : lb;
+}
+// The fluid id of this thread where a tile is shared by kBlock / THREADS workgroups.
+template <int THREADS, class SA>
+__device__ inline uint32_t split_tile_id(const SA& A, int skip) {
+  constexpr int kParts = kBlock / THREADS;
+  const int lb = logical_block(skip), tile = lb / kParts, part = lb % kParts;
+  return uint32_t(A.order ? A.order[tile] : tile) * kBlock + uint32_t(part) * THREADS + threadIdx.x;
 }
 
 // Division by a runtime constant d for 0 <= n < 2^31: q = (umulhi(n, m) + n) >> s with
@@ -610,29 +617,31 @@ __device__ inline double wave_sums(double s0, double s1, double s2, double s3) {
   return v;
 }
 
-// Sum of the per-workgroup partials (5 planes of nparts) by one workgroup of kBlock threads, in
-// a fixed order: strided per-thread sums, then the wave's sums, then the waves in order. Every
-// caller uses this one routine with the same thread count, so a step's sums do not depend on
-// where the reduction ran.
+// Sum of the per-workgroup partials (5 planes of nparts) by one workgroup, in a fixed order: strided
+// sums of kBlock slots, then each 64 slots' sums, then those in order. A workgroup of fewer threads
+// takes the slots in turn, so a step's sums do not depend on where the reduction ran.
+template <int THREADS>
 __device__ inline void reduce_partials(const double* partials, int nparts, double* out) {
   __shared__ double red[kBlock / 64][5];
-  double t[5] = {0, 0, 0, 0, 0};
-  int b = threadIdx.x;
-  for (; b + 3 * kBlock < nparts; b += 4 * kBlock) {
+  const int lane = threadIdx.x & 63;
+  for (int slot = threadIdx.x; slot < kBlock; slot += THREADS) {
+    double t[5] = {0, 0, 0, 0, 0};
+    int b = slot;
+    for (; b + 3 * kBlock < nparts; b += 4 * kBlock) {
 #pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      const double* p = partials + size_t(j) * nparts;
-      t[j] += ((p[b] + p[b + kBlock]) + (p[b + 2 * kBlock] + p[b + 3 * kBlock]));
+      for (int j = 0; j < 5; ++j) {
+        const double* p = partials + size_t(j) * nparts;
+        t[j] += ((p[b] + p[b + kBlock]) + (p[b + 2 * kBlock] + p[b + 3 * kBlock]));
+      }
     }
-  }
-  for (; b < nparts; b += kBlock) {
+    for (; b < nparts; b += kBlock) {
 #pragma unroll
-    for (int j = 0; j < 5; ++j) t[j] += partials[size_t(j) * nparts + b];
+      for (int j = 0; j < 5; ++j) t[j] += partials[size_t(j) * nparts + b];
+    }
+    const double v = wave_sums(t[0], t[1], t[2], t[3]), v4 = wave_sums(t[4], 0.0, 0.0, 0.0);
+    if (lane % 16 == 0) red[slot >> 6][lane / 16] = v;
+    if (lane == 0) red[slot >> 6][4] = v4;
   }
-  const double v = wave_sums(t[0], t[1], t[2], t[3]), v4 = wave_sums(t[4], 0.0, 0.0, 0.0);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane % 16 == 0) red[wave][lane / 16] = v;
-  if (lane == 0) red[wave][4] = v4;
   __syncthreads();
   if (threadIdx.x < 5) {
     double sum = red[0][threadIdx.x];
@@ -646,7 +655,7 @@ __device__ inline void reduce_partials(const double* partials, int nparts, doubl
 // (pinned: the kernel's own stores spare the copy and its wait, 8 of the 46 us of a one-step call).
 __global__ __launch_bounds__(kBlock) void k_finish_reduce(const double* partials, int nparts, double* ring, int rows,
                                                           double* host) {
-  reduce_partials(partials, nparts, ring + 5 * (rows - 1));
+  reduce_partials<kBlock>(partials, nparts, ring + 5 * (rows - 1));
   __syncthreads();
   if (host)
     for (int i = threadIdx.x; i < 5 * rows; i += kBlock) host[i] = ring[i];
@@ -655,10 +664,10 @@ __global__ __launch_bounds__(kBlock) void k_finish_reduce(const double* partials
 // A step's first kernel is launched with kXcd workgroups more when it also finishes the previous step's
 // sums (red_out): workgroup 0 does only that, the other seven return, so that no tile waits for the
 // sums, and the rest keep their XCD. True if the workgroup has no tile.
-template <class SA>
+template <int THREADS, class SA>
 __device__ inline bool finish_previous(const SA& A) {
   if (!A.red_out || blockIdx.x >= kXcd) return false;
-  if (blockIdx.x == 0) reduce_partials(A.red_in, A.red_n, A.red_out);
+  if (blockIdx.x == 0) reduce_partials<THREADS>(A.red_in, A.red_n, A.red_out);
   return true;
 }
 
@@ -713,13 +722,13 @@ __device__ inline R colour_of(uint32_t inf, const typename V4<R>::T& own, const 
   return rn_pack(rr, rp, R(1) / rm);
 }
 
-template <int P>
-__global__ __launch_bounds__(kBlock) void k_colour(StepArgs<P> A) {
+template <int P, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_colour(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
   using Off = typename Prec<P>::Off;
-  if (finish_previous(A)) return;
-  const uint32_t t = uint32_t(fluid_tile(A, A.red_out ? kXcd : 0)) * kBlock + threadIdx.x;
+  if (finish_previous<THREADS>(A)) return;
+  const uint32_t t = split_tile_id<THREADS>(A, A.red_out ? kXcd : 0);
   if (t >= uint32_t(A.nfluid)) return;
   const ListNode ln = ldx<Off>(A.fluid, t);
   const int n = ln.node;
@@ -922,6 +931,7 @@ __device__ inline bool finite(R v) {
 // Deterministic FP64 reduction over the workgroup of four sums and of the lanes with s[4] != 0: the
 // wave's sums, then the workgroup's waves in fixed order; one partial per workgroup (plain stores, no
 // fences or atomics). The sums are finished by reduce_partials, after the grid, in workgroup order.
+template <int THREADS>
 __device__ inline void block_reduce5(const double s[5], double* partials, int skip = 0) {
   __shared__ double red[kBlock / 64][5];
   const double v = wave_sums(s[0], s[1], s[2], s[3]);
@@ -933,7 +943,7 @@ __device__ inline void block_reduce5(const double s[5], double* partials, int sk
   if (threadIdx.x < 5) {
     double sum = red[0][threadIdx.x];
 #pragma unroll
-    for (int w = 1; w < kBlock / 64; ++w) sum += red[w][threadIdx.x];
+    for (int w = 1; w < THREADS / 64; ++w) sum += red[w][threadIdx.x];
     partials[size_t(threadIdx.x) * (gridDim.x - skip) + logical_block(skip)] = sum;
   }
 }
@@ -1129,14 +1139,14 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
 // when sigma = beta = 0: neither the force nor the recolouring uses a normal, rho^N is needed at the
 // node alone, and this one kernel is the whole step, forming rho^N from its own pull.
 // ---------------------------------------------------------------------------------------------
-template <int P, bool MOM, bool IFACE>
-__global__ __launch_bounds__(kBlock) void k_collide(StepArgs<P> A) {
+template <int P, bool MOM, bool IFACE, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_collide(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
   using Off = typename Prec<P>::Off;
-  if (!IFACE && finish_previous(A)) return;
+  if (!IFACE && finish_previous<THREADS>(A)) return;
   const int skip = !IFACE && A.red_out ? kXcd : 0;
-  const uint32_t t = uint32_t(fluid_tile(A, skip)) * kBlock + threadIdx.x;
+  const uint32_t t = split_tile_id<THREADS>(A, skip);
   double red5[5] = {0, 0, 0, 0, 0};
   if (t < uint32_t(A.nfluid)) {
     const ListNode ln = ldx<Off>(A.fluid, t);
@@ -1195,7 +1205,7 @@ __global__ __launch_bounds__(kBlock) void k_collide(StepArgs<P> A) {
     }
     collide_node<P, MOM>(A, t, n, inf, f, g, rn, cur, red5);
   }
-  if (!MOM && A.partials) block_reduce5(red5, A.partials, skip);
+  if (!MOM && A.partials) block_reduce5<THREADS>(red5, A.partials, skip);
 }
 
 // Zero at the solid nodes of the fields of lbm_moments (any may be null).
@@ -1241,7 +1251,7 @@ __global__ __launch_bounds__(kBlock) void k_state_sums(StepArgs<P> A) {
     red5[3] = double(C);
     red5[4] = (finite(s) && finite(a) && finite(C)) ? 0.0 : 1.0;
   }
-  block_reduce5(red5, A.partials);
+  block_reduce5<kBlock>(red5, A.partials);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -98,3 +98,25 @@ def test_moments_write_zero_at_solid_nodes(core):
     assert lib.lbm_moments(sim._h, None, None, None, only.data_ptr(), None) == 0
     torch.cuda.synchronize()
     assert torch.equal(only, out[3])
+
+
+# a cube of each way to share tiles among workgroups, and the node counts on both sides of the lines between
+@pytest.mark.parametrize("shape,precision", [((32, 32, 32), "fp64"), ((32, 32, 33), "fp64"), ((64, 32, 32), "fp64"),
+                                             ((41, 40, 40), "fp64"), ((32, 32, 32), "fp32"), ((32, 32, 33), "fp32"),
+                                             ((128, 48, 32), "fp32"), ((128, 48, 33), "fp32")])
+def test_sums_and_fields_at_the_workgroup_sizes(core, shape, precision):
+    """Three steps against the oracle. FP64 as above. FP32 storage: the populations of a node are
+    rounded once a step (6e-8 relative) and its arithmetic adds a few dozen roundings, none of which
+    grows in three steps, so 2e-5 of the largest value leaves two orders over their sum."""
+    import oracle
+
+    tol = FP64_TOL if precision == "fp64" else 2e-5
+    solid, red, kw = _sim(core, shape, porosity=1.0)
+    sim = core.Lbm(shape, solid=solid, rho_r0=red, rho_p0=1 - red, xi=0.01, precision=precision, tau_species=0.9, **kw)
+    ref = oracle.Oracle(shape, solid=solid, rho_r0=red, rho_p0=1 - red, xi=0.01, tau_c=0.9, **kw)
+    got, want = sim.step(3), ref.step(3)
+    assert np.abs(got[:, :4] - want[:, :4]).max() <= tol * np.abs(want[:, :4]).max()
+    assert not got[:, 4].any()
+    for k, (a, b) in enumerate(zip(sim.populations(), ref.get_state())):
+        err, bound = float(np.abs(a.cpu().numpy() - b).max()), tol * float(np.abs(b).max())
+        assert err <= bound, (k, err, bound)
