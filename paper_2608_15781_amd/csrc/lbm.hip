@@ -50,13 +50,33 @@ size_t real_bytes(int precision) { return precision == LBM_FP64 ? 8 : 4; }
 //   beyond, FP32 and the 2-byte storages are even (80^3 31.8 and 32.0) or lose (512 x 512 x 128 1932 -> 1941), and FP64,
 //     of whose collide workgroups only two fit a unit, gains (128^3 239 -> 230).
 // Workgroups of 64 threads are as fast as those of 128 up to 32^3 and cost the sums 2 us more.
+template <int P>
+constexpr int kSplitLarge = P % kWideMode == 0 ? 1 : 0;  // FP64
 int pull_split(const lbm_params& p, int nfluid) {
   constexpr int kPerUnit = 256 * 64;  // nodes of one wave per compute unit
   if (nfluid <= 2 * kPerUnit) return 1;
   if (nfluid <= 4 * kPerUnit) return 0;
-  return p.precision == LBM_FP64 || nfluid <= 12 * kPerUnit ? 1 : 0;
+  if (nfluid <= 12 * kPerUnit) return 1;
+  return p.precision == LBM_FP64 ? kSplitLarge<0> : kSplitLarge<1>;
 }
 constexpr int kMostSplit = 1;
+
+// Nontemporal stores of the new populations where the two states, which alternate, do not fit the 256 MB
+// last-level cache: a state then leaves it before it is read again, and stored past it leaves the room to
+// what is. Measured by the bytes of both states (us per step, ordinary and nontemporal stores): FP32
+// 112^3 169 MB 77 and 93, FP64 96^3 213 MB 91 and 102, FP32 128^3 253 MB 121 and 128, BF16 160^3
+// 295 MB even, FP64 112^3 339 MB 160 and 155, FP64 128^3 505 MB 231 and 222, FP32 512 x 512 x 128 4.4 GB
+// 1922 and 1877; the line lies between the last loss and the first gain.
+bool streams_state(const lbm_params& p, int nfluid) {
+  const double s = double(store_bytes(p.precision)), r = double(real_bytes(p.precision));
+  const double node = (p.species ? 26 : 19) * s + 4 * r + (p.species && s == 2 ? r : 0);
+  return 2 * node * double(nfluid) > 320e6;  // (0.6 million nodes or more, beyond pull_split's smaller lattices)
+}
+// Lattices of which the per-node vectors that one pass leaves to the next (colour scalars, normals) do not
+// stay in the last-level cache either: their stores are nontemporal too. 512 x 512 x 128 (18.4M fluid
+// nodes) FP32 1864 -> 1849 us, FP16 1563 -> 1547, 256^3 (8.4M) FP16 793 -> 787; at 192^3 (3.5M) even, FP64
+// 128^3 (1.05M) loses 0.5%.
+constexpr int kLargeNodes = 1 << 22;
 
 struct Layout {
   size_t info, wet, rhoN, nst, glen, state[2], partials, ring, lists[2], ids, counts, order, total;
@@ -205,6 +225,7 @@ struct lbm_ctx {
   int nfluid, next;      // list lengths
   int split, nb_pull;  // workgroups of the colour and collide passes: nb_fluid tiles, each shared by 2^split
   int nb_fluid, nb_ext;  // workgroups over each list (multiples of kXcd, 0 if empty)
+  bool stream_state, stream_vectors;  // the step's nontemporal stores
   bool ordered;          // fluid-list tiles launched in the order stored at L.order
   double* rows;          // pinned host memory: the ring rows of a chunk, written by k_finish_reduce
   void* static_scr;      // device address of the file-scope scratch array on this context's device
@@ -526,6 +547,7 @@ StepArgs<P> make_args(lbm_ctx* c, int src_buf) {
   A.nfluid = c->nfluid;
   A.ext = reinterpret_cast<const ListNode*>(c->ws + L.lists[1]);
   A.ids = reinterpret_cast<const IdWord*>(c->ws + L.ids);
+  A.stream_vectors = c->stream_vectors;
   A.order = c->ordered ? reinterpret_cast<const int*>(c->ws + L.order) : nullptr;
   A.next = c->next;
   A.info = reinterpret_cast<const uint32_t*>(c->ws + L.info);
@@ -589,10 +611,13 @@ void launch_colour(lbm_ctx* c, const StepArgs<P>& A, bool first = false) {
 template <int P, bool IFACE>
 void launch_collide(lbm_ctx* c, const StepArgs<P>& A) {
   const dim3 grid(c->nb_pull + (!IFACE && A.red_out ? kXcd : 0));
-  if (c->split)
-    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock / 2>), grid, dim3(kBlock / 2), 0, c->stream, A);
+  constexpr int kLarge = kBlock >> kSplitLarge<P>;  // lattices whose state is streamed have this size only
+  if (c->stream_state)
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kLarge, true>), grid, dim3(kLarge), 0, c->stream, A);
+  else if (c->split)
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock / 2, false>), grid, dim3(kBlock / 2), 0, c->stream, A);
   else
-    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock>), grid, dim3(kBlock), 0, c->stream, A);
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock, false>), grid, dim3(kBlock), 0, c->stream, A);
 }
 
 template <int P>
@@ -695,12 +720,12 @@ lbm_status launch_moments(lbm_ctx* c, void* rr, void* rp, void* rn, void* u, voi
   hipLaunchKernelGGL(k_clear_solids<R>, dim3((c->N + kBlock - 1) / kBlock), block, 0, c->stream, A.info, c->N, A.m_rr,
                      A.m_rp, A.m_rn, A.m_u, A.m_c);
   if (!uses_normals(c->p)) {
-    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false, kBlock>), gf, block, 0, c->stream, A);
+    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false, kBlock, false>), gf, block, 0, c->stream, A);
   } else {
     if (c->nb_fluid) launch_colour<P>(c, A);
     if (c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
     if (c->nb_fluid) hipLaunchKernelGGL(k_normal<P>, gf, block, 0, c->stream, A);
-    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, true, kBlock>), gf, block, 0, c->stream, A);
+    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, true, kBlock, false>), gf, block, 0, c->stream, A);
   }
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;
@@ -792,6 +817,8 @@ lbm_status launch_init(lbm_ctx* c, const uint8_t* d_solid, const uint8_t* d_reac
   c->nb_fluid = rounded_blocks(c->nfluid);
   c->nb_ext = rounded_blocks(c->next);
   c->split = pull_split(p, c->nfluid);
+  c->stream_state = streams_state(p, c->nfluid);
+  c->stream_vectors = c->nfluid >= kLargeNodes;
   c->nb_pull = c->nb_fluid << c->split;
   if (lbm_status s = build_tile_order(c); s != LBM_OK) return s;
   // The initial state goes into buffer 0 (make_args with src 1 writes buffer 0).

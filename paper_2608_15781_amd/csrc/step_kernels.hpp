@@ -79,6 +79,24 @@ __device__ inline T& refx(T* base, Off i) {
   else
     return base[i];
 }
+// Store of a value that no kernel reads before the caches have turned over (STREAM: nontemporal, so
+// that it does not displace what they hold) or that one soon does.
+template <bool STREAM, class T>
+__device__ inline void put(T& dst, const T& v) {
+  if constexpr (!STREAM) {
+    dst = v;
+  } else if constexpr (sizeof(T) == 2) {
+    __builtin_nontemporal_store(__builtin_bit_cast(uint16_t, v), reinterpret_cast<uint16_t*>(&dst));
+  } else if constexpr (sizeof(T) == 4) {
+    __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, v), reinterpret_cast<uint32_t*>(&dst));
+  } else {
+    static_assert(sizeof(T) == 8, "2, 4 or 8 bytes");
+    __builtin_nontemporal_store(__builtin_bit_cast(uint64_t, v), reinterpret_cast<uint64_t*>(&dst));
+  }
+}
+// Round one arm of a branch between such stores: without it the compiler merges the two arms into
+// ordinary stores.
+__device__ inline void keep_apart() { asm volatile("" ::: "memory"); }
 template <class R>
 struct Vec3 {
   R x, y, z;
@@ -101,6 +119,12 @@ __device__ inline void st4(R* p, Off n, R x, R y, R z, R w) {
   typename V4<R>::T v;
   v.x = x; v.y = y; v.z = z; v.w = w;
   refx<Off>(reinterpret_cast<typename V4<R>::T*>(p), n) = v;
+}
+template <class Off, class R>
+__device__ inline void st4_stream(R* p, Off n, R x, R y, R z, R w) {
+  typedef R V __attribute__((ext_vector_type(4)));
+  const V v = {x, y, z, w};
+  __builtin_nontemporal_store(v, reinterpret_cast<V*>(&refx<Off>(reinterpret_cast<typename V4<R>::T*>(p), n)));
 }
 
 // Uses all four components of a loaded vector. A load of which only some components are used is
@@ -475,6 +499,7 @@ struct StepArgs {
   const IdWord* ids;      // map from nodes to fluid ids (index into the state arrays)
   const int* order;       // optional launch order of the fluid-list tiles (null: list order)
   const uint32_t* info;
+  int stream_vectors;  // nontemporal stores of the per-node vectors that one pass leaves to the next
   // state in (pull source) and out
   const S* fin;  // 19 planes f^m
   const R* ain;  // per node 4-vector (e, vx, vy, vz), e = pack_frac(a, b)
@@ -882,8 +907,18 @@ __global__ __launch_bounds__(kBlock) void k_normal(StepArgs<P> A) {
   bool raw_set;
   normal_from_pairs<R>(d, inf, wv, A.eps, nv, len, raw, raw_set);
   if (raw_set && A.nraw) st4<Off>(A.nraw, t, raw[0], raw[1], raw[2], R(0));
-  ref3<Off>(A.nst, t) = {nv[0], nv[1], nv[2]};
-  refx<Off>(A.glen, t) = len;
+  Vec3<R>& nst = ref3<Off>(A.nst, t);
+  if (A.stream_vectors) {
+    keep_apart();
+    put<true>(nst.x, nv[0]);
+    put<true>(nst.y, nv[1]);
+    put<true>(nst.z, nv[2]);
+    put<true>(refx<Off>(A.glen, t), len);
+    keep_apart();
+  } else {
+    nst = {nv[0], nv[1], nv[2]};
+    refx<Off>(A.glen, t) = len;
+  }
 }
 
 // T^{-1} k* of Appendix A (eq. back_transformation_vector), regrouped with common
@@ -980,12 +1015,19 @@ __device__ inline R curvature_hg(const typename V4<R>::T& nsv, R eps, NbrN nbr) 
   return H * glen;
 }
 
+// One value to each of K planes.
+template <bool STREAM, class Off, int K, class S>
+__device__ inline void put_planes(S* planes, size_t ps, uint32_t t, const S (&v)[K]) {
+#pragma unroll
+  for (int i = 0; i < K; ++i) put<STREAM>(refx<Off>(planes + size_t(i) * ps, t), v[i]);
+}
+
 // The collision and the rest of the step at one fluid node x (fluid id t, node n, info word inf):
 // moments, forcing, central-moment collision, recolouring, reaction, species, store, and the
 // node's contribution to the FP64 sums (added to red5). f, g: the pulled populations; rn: rho^N(x)
 // (rn_value form); cur: (n*, H |G|) of x (n* = 0 where x has no normal). MOM writes the level-t
 // fields instead.
-template <int P, bool MOM>
+template <int P, bool MOM, bool STREAM>
 __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uint32_t inf,
                                     const typename Prec<P>::R f[19], const typename Prec<P>::R g[7],
                                     typename Prec<P>::R rn, const typename V4<typename Prec<P>::R>::T& cur,
@@ -1092,9 +1134,17 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
     const R aout = pack_frac((rr - delta) * irm, (rp + delta) * irm);
     const R vc = keep * A.beta * rr * rp * irm;
     const R v0 = has_n ? vc * n0 : R(0), v1 = has_n ? vc * n1 : R(0), v2 = has_n ? vc * n2 : R(0);
+    typename Prec<P>::S fo[19];
 #pragma unroll
-    for (int i = 0; i < 19; ++i) refx<Off>(A.fout + size_t(i) * A.ps, t) = Prec<P>::st(fs[i], R(D::w(i)), A.scale);
-    st4<Off>(A.aout, t, aout, v0, v1, v2);
+    for (int i = 0; i < 19; ++i) fo[i] = Prec<P>::st(fs[i], R(D::w(i)), A.scale);
+    put_planes<STREAM, Off>(A.fout, A.ps, t, fo);
+    if (STREAM && A.stream_vectors) {
+      keep_apart();
+      st4_stream<Off>(A.aout, t, aout, v0, v1, v2);
+      keep_apart();
+    } else {
+      st4<Off>(A.aout, t, aout, v0, v1, v2);
+    }
     bool ok = finite(fsum) && finite(aout) && finite(v0 + v1 + v2) && finite(rr) && finite(rp);
     if (A.species) {
       // BGK towards g^eq = w C (1 + 4 c.u_phys); at the inlet the populations are replaced by
@@ -1112,10 +1162,10 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
         gs += go[i];
       }
       if (Prec<P>::deviations) refx<Off>(A.cout, t) = gs;  // the deviation reference of the stored populations
+      typename Prec<P>::S gq[7];
 #pragma unroll
-      for (int i = 0; i < 7; ++i)
-        refx<Off>(A.gout + size_t(i) * A.ps, t) =
-            Prec<P>::st(go[i], Prec<P>::deviations ? R(D3Q7::w(i)) * gs : R(D3Q7::w(i)), A.gscale);
+      for (int i = 0; i < 7; ++i) gq[i] = Prec<P>::st(go[i], Prec<P>::deviations ? R(D3Q7::w(i)) * gs : R(D3Q7::w(i)), A.gscale);
+      put_planes<STREAM, Off>(A.gout, A.ps, t, gq);
       ok = ok && finite(gs);
     }
     red5[0] += double(rr);
@@ -1139,7 +1189,7 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
 // when sigma = beta = 0: neither the force nor the recolouring uses a normal, rho^N is needed at the
 // node alone, and this one kernel is the whole step, forming rho^N from its own pull.
 // ---------------------------------------------------------------------------------------------
-template <int P, bool MOM, bool IFACE, int THREADS>
+template <int P, bool MOM, bool IFACE, int THREADS, bool STREAM>
 __global__ __launch_bounds__(THREADS) void k_collide(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;
@@ -1203,7 +1253,7 @@ __global__ __launch_bounds__(THREADS) void k_collide(StepArgs<P> A) {
       R rm;
       rn = colour_of<R>(inf, own, nbr, [&](int i) { return f[i]; }, rm);
     }
-    collide_node<P, MOM>(A, t, n, inf, f, g, rn, cur, red5);
+    collide_node<P, MOM, STREAM>(A, t, n, inf, f, g, rn, cur, red5);
   }
   if (!MOM && A.partials) block_reduce5<THREADS>(red5, A.partials, skip);
 }

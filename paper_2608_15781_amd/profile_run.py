@@ -201,7 +201,7 @@ def report(args):
 
 
 BENCH_ARGS = "--steps 20 --warmup 5 --no-cpu --no-adjoint --no-side"
-STEP_KERNELS = ("lbm::k_colour<%d, 256>", "lbm::k_extrap<%d>", "lbm::k_normal<%d>", "lbm::k_collide<%d, false, true, 256>")
+STEP_KERNELS = ("lbm::k_colour<%d, 256>", "lbm::k_extrap<%d>", "lbm::k_normal<%d>", "lbm::k_collide<%d, false, true, 256, true>")
 
 
 def bench_trace(args):
