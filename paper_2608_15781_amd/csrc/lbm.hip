@@ -75,7 +75,9 @@ bool streams_state(const lbm_params& p, int nfluid) {
 // Lattices of which the per-node vectors that one pass leaves to the next (colour scalars, normals) do not
 // stay in the last-level cache either: their stores are nontemporal too. 512 x 512 x 128 (18.4M fluid
 // nodes) FP32 1864 -> 1849 us, FP16 1563 -> 1547, 256^3 (8.4M) FP16 793 -> 787; at 192^3 (3.5M) even, FP64
-// 128^3 (1.05M) loses 0.5%.
+// 128^3 (1.05M) loses 0.5%. They also launch the colour, extrap and normal passes in runs of tiles (run_block): 224^3
+// (5.6M) FP32 627 -> 622 us per step, 256^3 FP16 794 -> 787, 512 x 512 x 128 FP32 1882 -> 1858, FP16 1575 -> 1553; 192^3
+// even, 160^3 (2.0M) loses 1.7%, FP64 128^3 0.8%.
 constexpr int kLargeNodes = 1 << 22;
 
 struct Layout {
@@ -225,7 +227,7 @@ struct lbm_ctx {
   int nfluid, next;      // list lengths
   int split, nb_pull;  // workgroups of the colour and collide passes: nb_fluid tiles, each shared by 2^split
   int nb_fluid, nb_ext;  // workgroups over each list (multiples of kXcd, 0 if empty)
-  bool stream_state, stream_vectors;  // the step's nontemporal stores
+  bool stream_state, large;  // streams_state; at least kLargeNodes
   bool ordered;          // fluid-list tiles launched in the order stored at L.order
   double* rows;          // pinned host memory: the ring rows of a chunk, written by k_finish_reduce
   void* static_scr;      // device address of the file-scope scratch array on this context's device
@@ -547,7 +549,7 @@ StepArgs<P> make_args(lbm_ctx* c, int src_buf) {
   A.nfluid = c->nfluid;
   A.ext = reinterpret_cast<const ListNode*>(c->ws + L.lists[1]);
   A.ids = reinterpret_cast<const IdWord*>(c->ws + L.ids);
-  A.stream_vectors = c->stream_vectors;
+  A.stream_vectors = c->large;
   A.order = c->ordered ? reinterpret_cast<const int*>(c->ws + L.order) : nullptr;
   A.next = c->next;
   A.info = reinterpret_cast<const uint32_t*>(c->ws + L.info);
@@ -603,10 +605,29 @@ void use_fields(lbm_ctx* c, StepArgs<P>& A, void* fields) {
 template <int P>
 void launch_colour(lbm_ctx* c, const StepArgs<P>& A, bool first = false) {
   const dim3 grid(c->nb_pull + (first && A.red_out ? kXcd : 0));
-  if (c->split)
-    hipLaunchKernelGGL((k_colour<P, kBlock / 2>), grid, dim3(kBlock / 2), 0, c->stream, A);
+  constexpr int kLarge = kBlock >> kSplitLarge<P>;  // lattices of kLargeNodes have this size only
+  if (c->large)
+    hipLaunchKernelGGL((k_colour<P, kLarge, true>), grid, dim3(kLarge), 0, c->stream, A);
+  else if (c->split)
+    hipLaunchKernelGGL((k_colour<P, kBlock / 2, false>), grid, dim3(kBlock / 2), 0, c->stream, A);
   else
-    hipLaunchKernelGGL((k_colour<P, kBlock>), grid, dim3(kBlock), 0, c->stream, A);
+    hipLaunchKernelGGL((k_colour<P, kBlock, false>), grid, dim3(kBlock), 0, c->stream, A);
+}
+template <int P>
+void launch_extrap(lbm_ctx* c, const StepArgs<P>& A) {
+  if (!c->nb_ext) return;
+  if (c->large)
+    hipLaunchKernelGGL((k_extrap<P, true>), dim3(c->nb_ext), dim3(kBlock), 0, c->stream, A);
+  else
+    hipLaunchKernelGGL((k_extrap<P, false>), dim3(c->nb_ext), dim3(kBlock), 0, c->stream, A);
+}
+template <int P>
+void launch_normal(lbm_ctx* c, const StepArgs<P>& A) {
+  if (!c->nb_fluid) return;
+  if (c->large)
+    hipLaunchKernelGGL((k_normal<P, true>), dim3(c->nb_fluid), dim3(kBlock), 0, c->stream, A);
+  else
+    hipLaunchKernelGGL((k_normal<P, false>), dim3(c->nb_fluid), dim3(kBlock), 0, c->stream, A);
 }
 template <int P, bool IFACE>
 void launch_collide(lbm_ctx* c, const StepArgs<P>& A) {
@@ -622,16 +643,15 @@ void launch_collide(lbm_ctx* c, const StepArgs<P>& A) {
 
 template <int P>
 lbm_status enqueue_step(lbm_ctx* c, const StepArgs<P>& A, hipEvent_t* ev, bool fields, bool collide = true) {
-  const dim3 block(kBlock), gf(c->nb_fluid), ge(c->nb_ext);
   const bool iface = uses_normals(c->p);
   StepArgs<P> AC = A;
   if (!iface) AC.red_out = nullptr;
   if (ev) HIP_TRY(c, hipEventRecord(ev[0], c->stream));
   if ((iface || fields) && c->nb_fluid) launch_colour<P>(c, AC, iface);
   if (ev) HIP_TRY(c, hipEventRecord(ev[1], c->stream));
-  if ((iface || fields) && c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
+  if (iface || fields) launch_extrap<P>(c, A);
   if (ev) HIP_TRY(c, hipEventRecord(ev[2], c->stream));
-  if ((iface || fields) && c->nb_fluid) hipLaunchKernelGGL(k_normal<P>, gf, block, 0, c->stream, A);
+  if (iface || fields) launch_normal<P>(c, A);
   if (ev) HIP_TRY(c, hipEventRecord(ev[3], c->stream));
   if (collide && c->nb_fluid) {
     if (iface)
@@ -716,15 +736,15 @@ lbm_status launch_moments(lbm_ctx* c, void* rr, void* rp, void* rn, void* u, voi
   StepArgs<P> A = make_args<P>(c, c->cur);
   A.m_rr = static_cast<R*>(rr); A.m_rp = static_cast<R*>(rp); A.m_rn = static_cast<R*>(rn);
   A.m_u = static_cast<R*>(u); A.m_c = static_cast<R*>(cc);
-  const dim3 gf(c->nb_fluid), ge(c->nb_ext), block(kBlock);
+  const dim3 gf(c->nb_fluid), block(kBlock);
   hipLaunchKernelGGL(k_clear_solids<R>, dim3((c->N + kBlock - 1) / kBlock), block, 0, c->stream, A.info, c->N, A.m_rr,
                      A.m_rp, A.m_rn, A.m_u, A.m_c);
   if (!uses_normals(c->p)) {
     if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false, kBlock, false>), gf, block, 0, c->stream, A);
   } else {
     if (c->nb_fluid) launch_colour<P>(c, A);
-    if (c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
-    if (c->nb_fluid) hipLaunchKernelGGL(k_normal<P>, gf, block, 0, c->stream, A);
+    launch_extrap<P>(c, A);
+    launch_normal<P>(c, A);
     if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, true, kBlock, false>), gf, block, 0, c->stream, A);
   }
   HIP_TRY(c, hipGetLastError());
@@ -818,7 +838,7 @@ lbm_status launch_init(lbm_ctx* c, const uint8_t* d_solid, const uint8_t* d_reac
   c->nb_ext = rounded_blocks(c->next);
   c->split = pull_split(p, c->nfluid);
   c->stream_state = streams_state(p, c->nfluid);
-  c->stream_vectors = c->nfluid >= kLargeNodes;
+  c->large = c->nfluid >= kLargeNodes;
   c->nb_pull = c->nb_fluid << c->split;
   if (lbm_status s = build_tile_order(c); s != LBM_OK) return s;
   // The initial state goes into buffer 0 (make_args with src 1 writes buffer 0).
@@ -905,8 +925,8 @@ lbm_status launch_adj_step(lbm_ctx* c, const void* state, const void* fields, co
   // Forward fields of level t.
   if (!fields) {
     if (c->nb_fluid) launch_colour<P>(c, A);
-    if (c->nb_ext) hipLaunchKernelGGL(k_extrap<P>, ge, block, 0, c->stream, A);
-    if (c->nb_fluid) hipLaunchKernelGGL(k_normal<P>, gf, block, 0, c->stream, A);
+    launch_extrap<P>(c, A);
+    launch_normal<P>(c, A);
   }
   // Reverse pass. Every entry of lout a fluid node owns is written (see k_adj_collide).
   if (c->nb_fluid) {
