@@ -107,6 +107,7 @@ lbm_status lbm_state_bytes(const lbm_params* params, size_t* bytes);
  *   c0        double initial species concentration; NULL = 1 (ignored without species)
  * d_workspace: device memory of at least lbm_workspace_bytes, 256-byte aligned, owned by the
  * caller and used by the context until lbm_free. stream: hipStream_t or NULL (default stream).
+ * The context also holds 40 KB of pinned host memory, where the sums of the steps arrive.
  * Errors: LBM_ERR_ARG for invalid parameters or inputs (tau <= 0.5, negative sigma/beta/xi,
  * theta outside [0, pi], non-finite values, non-positive mixture density at a fluid node,
  * misaligned or too small workspace, params->fluid_nodes > 0 differing from the mask's fluid
@@ -174,6 +175,7 @@ lbm_status lbm_set_state(lbm_ctx* ctx, const void* d_src, int64_t steps_done);
  * launches of every step (colour, extrap, normal, collide) while enabled. Enabling resets the
  * totals. lbm_kernel_times writes the accumulated device time in milliseconds of each of the
  * four kernels (host array of 4) and the number of timed steps. Timing does not change results.
+ * Where sigma = beta = 0 the whole step is the collide launch and the other three are empty.
  * Errors: LBM_ERR_HIP if an event cannot be created or queried. */
 lbm_status lbm_set_profiling(lbm_ctx* ctx, int32_t enable);
 lbm_status lbm_kernel_times(lbm_ctx* ctx, double* kernel_ms, int64_t* steps);

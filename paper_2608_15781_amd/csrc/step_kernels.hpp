@@ -718,8 +718,9 @@ __device__ inline bool finish_previous(const SA& A) {
 // instructions or occupancy: with every source replaced by the node itself (the same loads, aligned)
 // it takes 417 us on a 512 x 512 x 128 porous lattice (18.5M fluid nodes, FP32), as a plain read of
 // its planes does, and with the real sources 576 us (118 B per node, 3.8 TB/s; 650 us before the
-// id words, the merged row edges and the 32-bit offsets); 128^3 FP32 37.2 -> 34.8 us, FP64 84.8 ->
-// 69.6 us. 94 VGPRs, five waves per SIMD; holding it to four costs 4%.
+// id words, the merged row edges and the 32-bit offsets, 560 with the stores and the launch order of
+// large lattices); 128^3 FP32 37.2 -> 34.8 us, FP64 84.8 -> 69.6 us (62 with half-size workgroups and
+// nontemporal stores of the state). 94 VGPRs, five waves per SIMD; holding it to four costs 4%.
 // ---------------------------------------------------------------------------------------------
 
 // rho^N (rn_value form) and rho^m of a node from its pulled populations fm(i) and the colour scalars
