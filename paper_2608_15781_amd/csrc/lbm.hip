@@ -61,16 +61,21 @@ int pull_split(const lbm_params& p, int nfluid) {
 }
 constexpr int kMostSplit = 1;
 
-// Nontemporal stores of the new populations where the two states, which alternate, do not fit the 256 MB
-// last-level cache: a state then leaves it before it is read again, and stored past it leaves the room to
-// what is. Measured by the bytes of both states (us per step, ordinary and nontemporal stores): FP32
-// 112^3 169 MB 77 and 93, FP64 96^3 213 MB 91 and 102, FP32 128^3 253 MB 121 and 128, BF16 160^3
-// 295 MB even, FP64 112^3 339 MB 160 and 155, FP64 128^3 505 MB 231 and 222, FP32 512 x 512 x 128 4.4 GB
-// 1922 and 1877; the line lies between the last loss and the first gain.
-bool streams_state(const lbm_params& p, int nfluid) {
+// Nontemporal stores of the new populations (0 none, 1 the species', 2 all) where the two states, which
+// alternate, do not fit the 256 MiB last-level cache: a state then leaves it before it is read again, and
+// stored past it leaves the room to what is. A little above the cache's size the species planes alone
+// are, which keeps the rest resident. Measured by the bytes of both states (us per step with none, the
+// species', all): FP32 112^3 169 MB 78, 87, 93; 124^3 230 MB 106, 111, 119; 128^3 253 MB 122, 120, 130; FP64 104^3
+// 271 MB 127, 121, 126; BF16 160^3 295 MB 202, 197, 202; FP32 136^3 302 MB 152, 149, 155; FP64 112^3 339 MB 161, 156,
+// 156; FP32 144^3 359 MB 180, 177, 179; BF16 176^3 392 MB 272, 270, 267; FP32 152^3 422 MB 210, 208, 208; 512 x
+// 512 x 128 4.4 GB 1922 without and 1877 with all. Without species planes the line for all is that of the
+// first measured gain over none.
+int streams_state(const lbm_params& p, int nfluid) {
   const double s = double(store_bytes(p.precision)), r = double(real_bytes(p.precision));
   const double node = (p.species ? 26 : 19) * s + 4 * r + (p.species && s == 2 ? r : 0);
-  return 2 * node * double(nfluid) > 320e6;  // (0.6 million nodes or more, beyond pull_split's smaller lattices)
+  const double both = 2 * node * double(nfluid);  // (0.5 million nodes or more, beyond pull_split's smaller lattices)
+  if (both > (p.species ? 370e6 : 320e6)) return 2;
+  return p.species && both > 248e6 ? 1 : 0;
 }
 // Lattices of which the per-node vectors that one pass leaves to the next (colour scalars, normals) do not
 // stay in the last-level cache either: their stores are nontemporal too. 512 x 512 x 128 (18.4M fluid
@@ -227,7 +232,8 @@ struct lbm_ctx {
   int nfluid, next;      // list lengths
   int split, nb_pull;  // workgroups of the colour and collide passes: nb_fluid tiles, each shared by 2^split
   int nb_fluid, nb_ext;  // workgroups over each list (multiples of kXcd, 0 if empty)
-  bool stream_state, large;  // streams_state; at least kLargeNodes
+  int stream_state;      // streams_state
+  bool large;            // at least kLargeNodes
   bool ordered;          // fluid-list tiles launched in the order stored at L.order
   double* rows;          // pinned host memory: the ring rows of a chunk, written by k_finish_reduce
   void* static_scr;      // device address of the file-scope scratch array on this context's device
@@ -633,12 +639,14 @@ template <int P, bool IFACE>
 void launch_collide(lbm_ctx* c, const StepArgs<P>& A) {
   const dim3 grid(c->nb_pull + (!IFACE && A.red_out ? kXcd : 0));
   constexpr int kLarge = kBlock >> kSplitLarge<P>;  // lattices whose state is streamed have this size only
-  if (c->stream_state)
-    hipLaunchKernelGGL((k_collide<P, false, IFACE, kLarge, true>), grid, dim3(kLarge), 0, c->stream, A);
+  if (c->stream_state == 2)
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kLarge, 2>), grid, dim3(kLarge), 0, c->stream, A);
+  else if (c->stream_state == 1)
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kLarge, 1>), grid, dim3(kLarge), 0, c->stream, A);
   else if (c->split)
-    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock / 2, false>), grid, dim3(kBlock / 2), 0, c->stream, A);
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock / 2, 0>), grid, dim3(kBlock / 2), 0, c->stream, A);
   else
-    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock, false>), grid, dim3(kBlock), 0, c->stream, A);
+    hipLaunchKernelGGL((k_collide<P, false, IFACE, kBlock, 0>), grid, dim3(kBlock), 0, c->stream, A);
 }
 
 template <int P>
@@ -740,12 +748,12 @@ lbm_status launch_moments(lbm_ctx* c, void* rr, void* rp, void* rn, void* u, voi
   hipLaunchKernelGGL(k_clear_solids<R>, dim3((c->N + kBlock - 1) / kBlock), block, 0, c->stream, A.info, c->N, A.m_rr,
                      A.m_rp, A.m_rn, A.m_u, A.m_c);
   if (!uses_normals(c->p)) {
-    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false, kBlock, false>), gf, block, 0, c->stream, A);
+    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, false, kBlock, 0>), gf, block, 0, c->stream, A);
   } else {
     if (c->nb_fluid) launch_colour<P>(c, A);
     launch_extrap<P>(c, A);
     launch_normal<P>(c, A);
-    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, true, kBlock, false>), gf, block, 0, c->stream, A);
+    if (c->nb_fluid) hipLaunchKernelGGL((k_collide<P, true, true, kBlock, 0>), gf, block, 0, c->stream, A);
   }
   HIP_TRY(c, hipGetLastError());
   return LBM_OK;

@@ -1041,7 +1041,7 @@ __device__ inline void put_planes(S* planes, size_t ps, uint32_t t, const S (&v)
 // node's contribution to the FP64 sums (added to red5). f, g: the pulled populations; rn: rho^N(x)
 // (rn_value form); cur: (n*, H |G|) of x (n* = 0 where x has no normal). MOM writes the level-t
 // fields instead.
-template <int P, bool MOM, bool STREAM>
+template <int P, bool MOM, int STREAM>
 __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uint32_t inf,
                                     const typename Prec<P>::R f[19], const typename Prec<P>::R g[7],
                                     typename Prec<P>::R rn, const typename V4<typename Prec<P>::R>::T& cur,
@@ -1151,8 +1151,8 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
     typename Prec<P>::S fo[19];
 #pragma unroll
     for (int i = 0; i < 19; ++i) fo[i] = Prec<P>::st(fs[i], R(D::w(i)), A.scale);
-    put_planes<STREAM, Off>(A.fout, A.ps, t, fo);
-    if (STREAM && A.stream_vectors) {
+    put_planes<STREAM == 2, Off>(A.fout, A.ps, t, fo);
+    if (STREAM == 2 && A.stream_vectors) {
       keep_apart();
       st4_stream<Off>(A.aout, t, aout, v0, v1, v2);
       keep_apart();
@@ -1179,7 +1179,7 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
       typename Prec<P>::S gq[7];
 #pragma unroll
       for (int i = 0; i < 7; ++i) gq[i] = Prec<P>::st(go[i], Prec<P>::deviations ? R(D3Q7::w(i)) * gs : R(D3Q7::w(i)), A.gscale);
-      put_planes<STREAM, Off>(A.gout, A.ps, t, gq);
+      put_planes<STREAM != 0, Off>(A.gout, A.ps, t, gq);
       ok = ok && finite(gs);
     }
     red5[0] += double(rr);
@@ -1202,8 +1202,9 @@ __device__ inline void collide_node(const StepArgs<P>& A, uint32_t t, int n, uin
 // set-up, with interfaces round eight nucleation sites, 43 -> 40 us, waves without such nodes the same). IFACE = false, chosen
 // when sigma = beta = 0: neither the force nor the recolouring uses a normal, rho^N is needed at the
 // node alone, and this one kernel is the whole step, forming rho^N from its own pull.
+// STREAM: nontemporal stores of the species (1) or of all populations (2).
 // ---------------------------------------------------------------------------------------------
-template <int P, bool MOM, bool IFACE, int THREADS, bool STREAM>
+template <int P, bool MOM, bool IFACE, int THREADS, int STREAM>
 __global__ __launch_bounds__(THREADS) void k_collide(StepArgs<P> A) {
   using R = typename Prec<P>::R;
   using D = D3Q19;

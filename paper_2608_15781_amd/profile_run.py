@@ -203,7 +203,7 @@ def report(args):
 BENCH_ARGS = "--steps 20 --warmup 5 --no-cpu --no-adjoint --no-side"
 # as launched on the 512^3 headline lattice
 STEP_KERNELS = ("lbm::k_colour<%d, 256, true>", "lbm::k_extrap<%d, true>", "lbm::k_normal<%d, true>",
-                "lbm::k_collide<%d, false, true, 256, true>")
+                "lbm::k_collide<%d, false, true, 256, 2>")
 
 
 def bench_trace(args):
