@@ -14,6 +14,7 @@
 
 #include "lbm.h"
 #include "lattice.hpp"
+#include "offsets.hpp"
 #include "precision.hpp"
 #include "step_kernels.hpp"
 #include "adjoint_kernels.hpp"
@@ -94,14 +95,19 @@ struct Layout {
 
 size_t plane_stride(const lbm_params& p);
 
-// Whether some byte offset that the kernels form passes 32 bits. The largest are a population of the
-// pair's upper plane (the two planes of a pair are at most five apart, ld_pull), the 4-vectors per
-// fluid id, the pairs per node and the launch lists. FP32 lattices of up to 178 million fluid nodes
-// and FP64 ones of up to 89 million stay within them. On the 512^3 porous mask the 32-bit offsets
-// take a tenth off the instructions of the colour and collide passes.
-bool use_wide_offsets(const lbm_params& p) {
-  const size_t N = size_t(p.nx) * p.ny * p.nz, ps = plane_stride(p), s = store_bytes(p.precision), r = real_bytes(p.precision);
-  return std::max(std::max(6 * s * ps, 4 * r * ps), std::max(2 * r * N, sizeof(ListNode) * N)) >= (size_t(1) << 32);
+// The storage modes of the forward and the reverse kernels: the storage, plus kWideMode where 32-bit
+// byte offsets do not suffice. FP32 lattices of up to 178 million fluid nodes and FP64 ones of up to 89
+// million stay within them in both; the 2-byte storages up to 268 million in the step and up to 178 million
+// in the reverse pass, whose populations have 4 bytes. On the 512^3 porous mask the 32-bit offsets take a
+// tenth off the instructions of the colour and collide passes.
+static_assert(sizeof(ListNode) == 8, "counted in step_offsets");
+int step_mode(const lbm_params& p) {
+  const size_t N = size_t(p.nx) * p.ny * p.nz;
+  return p.precision + (wide(step_offsets(N, plane_stride(p), store_bytes(p.precision), real_bytes(p.precision))) ? kWideMode : 0);
+}
+int adjoint_mode(const lbm_params& p) {
+  const size_t N = size_t(p.nx) * p.ny * p.nz;
+  return p.precision + (wide(adjoint_offsets(N, plane_stride(p), store_bytes(p.precision), real_bytes(p.precision))) ? kWideMode : 0);
 }
 
 // Whether the step uses the interface normal: in the force (sigma) or the recolouring (beta).
@@ -222,7 +228,7 @@ AdjLayout make_adj_layout(const lbm_params& p) {
 
 struct lbm_ctx {
   lbm_params p;
-  int mode;  // the kernels' storage mode: p.precision, plus kWideMode where 32-bit byte offsets do not suffice
+  int mode, adj_mode;  // storage modes of the forward and the reverse kernels
   int N;
   Layout L;
   char* ws;
@@ -965,18 +971,20 @@ lbm_status check_adjoint_buffers(lbm_ctx* c, const void* state, const void* fiel
   return LBM_OK;
 }
 
-// fn<mode>(ctx, ...) for the context's mode.
-#define DISPATCH(ctx, fn, ...)                                                  \
-  switch ((ctx)->mode) {                                                        \
-    case LBM_FP64: return fn<LBM_FP64>((ctx), __VA_ARGS__);                     \
-    case LBM_FP32: return fn<LBM_FP32>((ctx), __VA_ARGS__);                     \
-    case LBM_FP16_DEV: return fn<LBM_FP16_DEV>((ctx), __VA_ARGS__);             \
-    case LBM_BF16_DEV: return fn<LBM_BF16_DEV>((ctx), __VA_ARGS__);             \
+// fn<mode>(ctx, ...) for the context's storage mode of the forward (DISPATCH) or the reverse kernels.
+#define DISPATCH_MODE(mode, ctx, fn, ...)                                                   \
+  switch (mode) {                                                                           \
+    case LBM_FP64: return fn<LBM_FP64>((ctx), __VA_ARGS__);                                 \
+    case LBM_FP32: return fn<LBM_FP32>((ctx), __VA_ARGS__);                                 \
+    case LBM_FP16_DEV: return fn<LBM_FP16_DEV>((ctx), __VA_ARGS__);                         \
+    case LBM_BF16_DEV: return fn<LBM_BF16_DEV>((ctx), __VA_ARGS__);                         \
     case kWideMode + LBM_FP64: return fn<kWideMode + LBM_FP64>((ctx), __VA_ARGS__);         \
     case kWideMode + LBM_FP32: return fn<kWideMode + LBM_FP32>((ctx), __VA_ARGS__);         \
     case kWideMode + LBM_FP16_DEV: return fn<kWideMode + LBM_FP16_DEV>((ctx), __VA_ARGS__); \
-    default: return fn<kWideMode + LBM_BF16_DEV>((ctx), __VA_ARGS__);           \
+    default: return fn<kWideMode + LBM_BF16_DEV>((ctx), __VA_ARGS__);                       \
   }
+#define DISPATCH(ctx, fn, ...) DISPATCH_MODE((ctx)->mode, ctx, fn, __VA_ARGS__)
+#define DISPATCH_ADJOINT(ctx, fn, ...) DISPATCH_MODE((ctx)->adj_mode, ctx, fn, __VA_ARGS__)
 
 lbm_status step_once(lbm_ctx* c, int slot, void* fields) { DISPATCH(c, launch_step, slot, fields); }
 lbm_status init_once(lbm_ctx* c, const uint8_t* solid, const uint8_t* react, const double* theta, double theta_uniform,
@@ -1058,7 +1066,8 @@ lbm_status lbm_init(const lbm_params* params, const uint8_t* solid, const double
   lbm_ctx* c = new (std::nothrow) lbm_ctx();
   if (!c) return LBM_ERR_ALLOC;
   c->p = *params;
-  c->mode = params->precision + (use_wide_offsets(*params) ? kWideMode : 0);
+  c->mode = step_mode(*params);
+  c->adj_mode = adjoint_mode(*params);
   c->N = int(N);
   c->L = L;
   c->ws = static_cast<char*>(d_workspace);
@@ -1294,7 +1303,7 @@ lbm_status lbm_adjoint_bytes(const lbm_params* params, size_t* adj_bytes, size_t
 lbm_status lbm_adjoint_seed(lbm_ctx* c, const void* d_state, void* d_adj) {
   if (!c) return LBM_ERR_ARG;
   if (!d_state || !d_adj) return fail(c, LBM_ERR_ARG, "state and adjoint buffers are required");
-  DISPATCH(c, launch_adj_seed, d_state, d_adj);
+  DISPATCH_ADJOINT(c, launch_adj_seed, d_state, d_adj);
 }
 
 lbm_status lbm_adjoint_step(lbm_ctx* c, const void* d_state, const void* d_adj_in, void* d_adj_out, void* d_scratch,
@@ -1305,7 +1314,7 @@ lbm_status lbm_adjoint_step(lbm_ctx* c, const void* d_state, const void* d_adj_i
   const lbm_status chk = check_adjoint_buffers(c, d_state, nullptr, d_adj_in, d_adj_out, d_scratch);
   if (chk != LBM_OK) return chk;
   const void* no_fields = nullptr;
-  DISPATCH(c, launch_adj_step, d_state, no_fields, d_adj_in, d_adj_out, d_scratch, d_grad_theta, d_grad_xi);
+  DISPATCH_ADJOINT(c, launch_adj_step, d_state, no_fields, d_adj_in, d_adj_out, d_scratch, d_grad_theta, d_grad_xi);
 }
 
 lbm_status lbm_adjoint_step_fields(lbm_ctx* c, const void* d_state, const void* d_fields, const void* d_adj_in,
@@ -1315,7 +1324,7 @@ lbm_status lbm_adjoint_step_fields(lbm_ctx* c, const void* d_state, const void* 
     return fail(c, LBM_ERR_ARG, "all buffers are required");
   const lbm_status chk = check_adjoint_buffers(c, d_state, d_fields, d_adj_in, d_adj_out, d_scratch);
   if (chk != LBM_OK) return chk;
-  DISPATCH(c, launch_adj_step, d_state, d_fields, d_adj_in, d_adj_out, d_scratch, d_grad_theta, d_grad_xi);
+  DISPATCH_ADJOINT(c, launch_adj_step, d_state, d_fields, d_adj_in, d_adj_out, d_scratch, d_grad_theta, d_grad_xi);
 }
 
 lbm_status lbm_adjoint_step_static(lbm_ctx* c, const void* d_state, const void* d_adj_in, void* d_adj_out,
@@ -1335,7 +1344,7 @@ lbm_status lbm_adjoint_step_static(lbm_ctx* c, const void* d_state, const void* 
   const lbm_status chk = check_adjoint_buffers(c, d_state, nullptr, d_adj_in, d_adj_out, scr);
   if (chk != LBM_OK) return chk;
   const void* no_fields = nullptr;
-  DISPATCH(c, launch_adj_step, d_state, no_fields, d_adj_in, d_adj_out, scr, d_grad_theta, d_grad_xi);
+  DISPATCH_ADJOINT(c, launch_adj_step, d_state, no_fields, d_adj_in, d_adj_out, scr, d_grad_theta, d_grad_xi);
 }
 
 size_t lbm_adjoint_static_scratch_bytes(void) { return kStaticScratchBytes; }

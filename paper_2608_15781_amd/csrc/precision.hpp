@@ -7,7 +7,7 @@
 // one register and the base stays in scalar registers, where 64-bit per-lane addresses take a
 // shift, a sign extension and a 64-bit add (or, for a selected plane, a 64-bit product at a quarter
 // of the rate) on every gather. Modes 4..7 are the same storages with 64-bit offsets, for lattices
-// whose arrays pass 4 GB (see use_wide_offsets in lbm.hip).
+// whose arrays pass 4 GB (see offsets.hpp).
 #pragma once
 
 #include <hip/hip_runtime.h>
