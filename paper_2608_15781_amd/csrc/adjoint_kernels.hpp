@@ -188,13 +188,14 @@ __global__ __launch_bounds__(kBlock) void k_adj_seed(StepArgs<P> A, typename Pre
 // Reverse of the collide kernel at one fluid node (forward arithmetic recomputed as in k_collide).
 // Register budget: the pull sources and the species populations, needed again only at the end,
 // wait in LDS (25 KB per workgroup in FP32), and every plane is addressed by a uniform base and
-// a 32-bit offset, which brings the FP32 kernel to 119 VGPRs (165 with 64-bit addresses) and
-// four waves per SIMD without spills (three are requested below); FP64 keeps one wave. Bound by
+// an offset, which brings the FP32 and 2-byte kernels to 118 VGPRs (119 with 64-bit offsets; 165 with
+// an address per lane) and four waves per SIMD without spills (three are requested below). FP64 takes
+// 236 VGPRs and two waves, with offsets of either width: bound to three it spills 98. Bound by
 // the latency of its dependent rounds of loads (ids, normals, adjoint planes) at that occupancy:
 // asking for all adjoint planes with the first round needs 131 VGPRs and cost 0.9% of the pass.
 // ---------------------------------------------------------------------------------------------
 template <int P>
-__global__ __launch_bounds__(kBlock, P == 0 ? 1 : 3) void k_adj_collide(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
+__global__ __launch_bounds__(kBlock, P % kWideMode == 0 ? 1 : 3) void k_adj_collide(StepArgs<P> A, AdjArgs<typename Prec<P>::R> J) {
   using R = typename Prec<P>::R;
   using Off = typename Prec<P>::Off;
   using D = D3Q19;
