@@ -465,6 +465,8 @@ __device__ inline void row_gather(const RowLanes& lanes, uint32_t inf, Index idx
   const bool below = lanes.below, above = lanes.above;
   const uint32_t belowm = below ? ~0u : 0u, abovem = above ? ~0u : 0u;
 #pragma unroll
+  for (int r = 0; r < 5; ++r) edge[r] = T{};
+#pragma unroll
   for (int i = 0; i < 18; ++i)
     if (D::cx[i] == 0 && need(i)) out[i] = ld(idx(i));
 #pragma unroll
@@ -473,7 +475,6 @@ __device__ inline void row_gather(const RowLanes& lanes, uint32_t inf, Index idx
     if (!need(ip)) continue;
     const uint32_t lack_p = SOLID_OWN ? ~(belowm | bit_mask(inf, ip)) : ~belowm;
     const uint32_t lack_m = SOLID_OWN ? ~(abovem | bit_mask(inf, im)) : ~abovem;
-    edge[r] = T{};
     if (lack_p | lack_m) edge[r] = ld(blend(lack_p, idx(ip), idx(im)));
   }
 }
