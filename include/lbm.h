@@ -180,6 +180,10 @@ lbm_status lbm_set_state(lbm_ctx* ctx, const void* d_src, int64_t steps_done);
 lbm_status lbm_set_profiling(lbm_ctx* ctx, int32_t enable);
 lbm_status lbm_kernel_times(lbm_ctx* ctx, double* kernel_ms, int64_t* steps);
 
+/* From now on this context takes the kernels with 64-bit array offsets, as lattices whose arrays pass 4 GB
+ * do by themselves. Results do not change: the call lets the two forms be compared on small lattices. */
+lbm_status lbm_use_wide_offsets(lbm_ctx* ctx);
+
 /* Discrete adjoint of the step, for gradients of the gas production L = m^p(T) - m^p(0)
  * (eqs. product_mass, production_rate) with respect to the per-node contact angle theta(x)
  * (eq. realigned_normal_vectors) and the reaction rate xi (eq. reactive_boundary_condition_*).

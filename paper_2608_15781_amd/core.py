@@ -22,7 +22,7 @@ EXPORTED = ["lbm_version", "lbm_workspace_bytes", "lbm_state_bytes", "lbm_init",
             "lbm_set_profiling", "lbm_kernel_times", "lbm_adjoint_bytes", "lbm_adjoint_seed", "lbm_adjoint_step",
             "lbm_steps_done", "lbm_free", "lbm_last_error", "lbm_fields_bytes", "lbm_step_fields",
             "lbm_adjoint_step_fields", "lbm_step_from", "lbm_state_sums", "lbm_adjoint_step_static",
-            "lbm_adjoint_static_scratch_bytes"]
+            "lbm_adjoint_static_scratch_bytes", "lbm_use_wide_offsets"]
 KERNELS = ("colour", "extrap", "normal", "collide")
 
 
@@ -86,6 +86,7 @@ def lib():
         L.lbm_adjoint_step.argtypes = [vp, vp, vp, vp, vp, vp, vp]
         L.lbm_set_profiling.argtypes = [vp, i32]
         L.lbm_kernel_times.argtypes = [vp, vp, vp]
+        L.lbm_use_wide_offsets.argtypes = [vp]
         L.lbm_steps_done.argtypes = [vp]
         L.lbm_steps_done.restype = i64
         L.lbm_free.argtypes = [vp]
@@ -446,6 +447,10 @@ class Lbm:
         n = ctypes.c_int64()
         self._check(lib().lbm_kernel_times(self._h, ms, ctypes.byref(n)), self._h)
         return dict(zip(KERNELS, list(ms))), int(n.value)
+
+    def use_wide_offsets(self):
+        """The kernels with 64-bit array offsets from now on (results do not change)."""
+        self._check(lib().lbm_use_wide_offsets(self._h), self._h)
 
     def set_state(self, buf, steps_done):
         if buf.numel() != self.state_bytes or buf.device != self.device:

@@ -1291,6 +1291,12 @@ lbm_status lbm_kernel_times(lbm_ctx* c, double* kernel_ms, int64_t* steps) {
   return LBM_OK;
 }
 
+lbm_status lbm_use_wide_offsets(lbm_ctx* c) {
+  if (!c) return LBM_ERR_ARG;
+  c->mode = c->adj_mode = c->p.precision + kWideMode;
+  return LBM_OK;
+}
+
 lbm_status lbm_adjoint_bytes(const lbm_params* params, size_t* adj_bytes, size_t* scratch_bytes) {
   lbm_status s = check_params(params, g_err, sizeof(g_err));
   if (s != LBM_OK) return s;
