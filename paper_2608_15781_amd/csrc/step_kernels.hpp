@@ -1292,11 +1292,13 @@ __global__ __launch_bounds__(THREADS) void k_collide(StepArgs<P> A) {
   if (!MOM && A.partials) block_reduce5<THREADS>(red5, A.partials, skip);
 }
 
-// Zero at the solid nodes of the fields of lbm_moments (any may be null).
+// Zeros for the fields of lbm_moments (any may be null), whose fluid nodes the collide pass then writes: at the
+// solid nodes, or with info = null at every node. Whole lines take no info words and stream; the solid
+// nodes alone write less where they are few (clears_whole in lbm.hip).
 template <class R>
-__global__ __launch_bounds__(kBlock) void k_clear_solids(const uint32_t* info, int N, R* rr, R* rp, R* rn, R* u, R* c) {
+__global__ __launch_bounds__(kBlock) void k_clear(const uint32_t* info, int N, R* rr, R* rp, R* rn, R* u, R* c) {
   const size_t n = size_t(blockIdx.x) * kBlock + threadIdx.x, count = size_t(N);
-  if (n >= count || (info[n] & kFluid)) return;
+  if (n >= count || (info && (info[n] & kFluid))) return;
   if (rr) rr[n] = R(0);
   if (rp) rp[n] = R(0);
   if (rn) rn[n] = R(0);
