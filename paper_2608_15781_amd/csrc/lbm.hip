@@ -429,17 +429,25 @@ __global__ void k_init_wet(Geom g, const uint8_t* solid, const uint32_t* info, c
   st4<size_t>(wet, fluid_id(ids, n), R(sx * il), R(sy * il), R(sz * il), R(cos(th)));
 }
 
-// Dense copy (4 reals per node, node-major) of the per-fluid-id wetting data; zero at solids.
+// Dense copy (4 reals per node, node-major) of the per-fluid-id wetting data; zero at solids. Two nodes to a
+// thread, so that their chains of id word and vector overlap.
+constexpr int kWetNodes = 2;
 template <class R>
-__global__ void k_wet_dense(int N, const uint32_t* info, const IdWord* ids, const R* wet, R* out) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  if (info[n] & kFluid) {
-    const typename V4<R>::T v = ld4<size_t>(wet, fluid_id(ids, n));
-    st4<size_t>(out, n, v.x, v.y, v.z, v.w);
-  } else {
-    st4<size_t>(out, n, R(0), R(0), R(0), R(0));
+__global__ __launch_bounds__(kBlock) void k_wet_dense(int N, const IdWord* ids, const R* wet, R* out) {
+  const size_t n0 = size_t(blockIdx.x) * kBlock * kWetNodes + threadIdx.x, count = size_t(N);
+  IdWord word[kWetNodes];
+#pragma unroll
+  for (int k = 0; k < kWetNodes; ++k) word[k] = n0 + k * kBlock < count ? ids[(n0 + k * kBlock) >> 5] : IdWord{0, 0};
+  typename V4<R>::T v[kWetNodes];
+#pragma unroll
+  for (int k = 0; k < kWetNodes; ++k) {
+    v[k].x = v[k].y = v[k].z = v[k].w = R(0);
+    const uint32_t n = uint32_t(n0 + k * kBlock);
+    if (is_fluid(word[k], n)) v[k] = ld4<size_t>(wet, fluid_before(word[k], n));
   }
+#pragma unroll
+  for (int k = 0; k < kWetNodes; ++k)
+    if (n0 + k * kBlock < count) st4<size_t>(out, n0 + k * kBlock, v[k].x, v[k].y, v[k].z, v[k].w);
 }
 
 // S_0 = f^eq(rho^k_0, 0) per colour: f^m = w (rho^r + rho^p), a = rho^r / rho^m, v = 0, g = w C_0.
@@ -1238,14 +1246,13 @@ lbm_status lbm_geometry(lbm_ctx* c, void* d_info, void* d_wet) {
   const size_t N = c->N;
   if (d_info) HIP_TRY(c, hipMemcpyAsync(d_info, c->ws + c->L.info, 4 * N, hipMemcpyDeviceToDevice, c->stream));
   if (d_wet) {
-    const int tb = 256, gb = int((N + tb - 1) / tb);
+    const int tb = kBlock, gb = int((N + kBlock * kWetNodes - 1) / (kBlock * kWetNodes));
     const IdWord* ids = reinterpret_cast<const IdWord*>(c->ws + c->L.ids);
-    const uint32_t* info = reinterpret_cast<const uint32_t*>(c->ws + c->L.info);
     if (c->p.precision == LBM_FP64)
-      hipLaunchKernelGGL(k_wet_dense<double>, dim3(gb), dim3(tb), 0, c->stream, int(N), info, ids,
+      hipLaunchKernelGGL(k_wet_dense<double>, dim3(gb), dim3(tb), 0, c->stream, int(N), ids,
                          reinterpret_cast<const double*>(c->ws + c->L.wet), static_cast<double*>(d_wet));
     else
-      hipLaunchKernelGGL(k_wet_dense<float>, dim3(gb), dim3(tb), 0, c->stream, int(N), info, ids,
+      hipLaunchKernelGGL(k_wet_dense<float>, dim3(gb), dim3(tb), 0, c->stream, int(N), ids,
                          reinterpret_cast<const float*>(c->ws + c->L.wet), static_cast<float*>(d_wet));
     HIP_TRY(c, hipGetLastError());
   }

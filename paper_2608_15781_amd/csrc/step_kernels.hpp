@@ -337,6 +337,7 @@ struct IdWord {
   uint32_t fluid, before;
 };
 __device__ inline uint32_t fluid_before(IdWord w, uint32_t n) { return __popc(w.fluid & ((1u << (n & 31u)) - 1u)) + w.before; }
+__device__ inline bool is_fluid(IdWord w, uint32_t n) { return (w.fluid >> (n & 31u)) & 1u; }
 __device__ inline uint32_t fluid_id(const IdWord* ids, int n) { return fluid_before(ids[n >> 5], uint32_t(n)); }
 
 // Fluid ids of the 18 pull sources x - c_i of fluid node t, the node's own id where the source is
@@ -1351,25 +1352,39 @@ __global__ __launch_bounds__(kBlock) void k_expand(StepArgs<P> A, typename Prec<
   const int n = logical_block() * kBlock + threadIdx.x;
   if (n >= A.N) return;
   const size_t N = A.N;
-  const bool fluid = A.info[n] & kFluid;
-  const size_t fi = fluid ? fluid_id(A.ids, n) : 0;
+  using Off = typename Prec<P>::Off;
+  const IdWord word = A.ids[n >> 5];
+  const bool fluid = is_fluid(word, uint32_t(n));
+  const uint32_t fi = fluid ? fluid_before(word, uint32_t(n)) : 0;
+  // Every load of the node before the first store (a solid node loads nothing), and the id word, which holds the
+  // fluid bit, instead of an info word beside it: FP32 128^3 131 -> 116 us, 256^3 1030 -> 855; FP16 128^3 126 -> 106.
   typename V4<R>::T av;
   av.x = av.y = av.z = av.w = R(0);
-  if (fluid) av = ld4<size_t>(A.ain, fi);
+  R fm[19], g[7];
+#pragma unroll
+  for (int i = 0; i < 19; ++i) fm[i] = R(0);
+#pragma unroll
+  for (int i = 0; i < 7; ++i) g[i] = R(0);
+  if (fluid) {
+    av = ld4<Off>(A.ain, fi);
+#pragma unroll
+    for (int i = 0; i < 19; ++i) fm[i] = Prec<P>::ld(ldx<Off>(A.fin + size_t(i) * A.ps, fi), R(D::w(i)), A.inv_scale);
+    if (go && A.species)
+#pragma unroll
+      for (int i = 0; i < 7; ++i) g[i] = ld_species(A, i, fi);
+  }
   const R v0 = av.y, v1 = av.z, v2 = av.w;
   R a, b;
   unpack_frac(av.x, a, b);
 #pragma unroll
   for (int i = 0; i < 19; ++i) {
-    const R fm = fluid ? Prec<P>::ld(A.fin[size_t(i) * A.ps + fi], R(D::w(i)), A.inv_scale) : R(0);
     const R kv = R(D::w_over_len(i)) * (R(D::cx[i]) * v0 + R(D::cy[i]) * v1 + R(D::cz[i]) * v2);
-    fr[size_t(i) * N + n] = fluid ? a * fm + kv : R(0);
-    fp[size_t(i) * N + n] = fluid ? b * fm - kv : R(0);
+    fr[size_t(i) * N + n] = fluid ? a * fm[i] + kv : R(0);
+    fp[size_t(i) * N + n] = fluid ? b * fm[i] - kv : R(0);
   }
   if (go) {
 #pragma unroll
-    for (int i = 0; i < 7; ++i)
-      go[size_t(i) * N + n] = (fluid && A.species) ? ld_species(A, i, fi) : R(0);
+    for (int i = 0; i < 7; ++i) go[size_t(i) * N + n] = g[i];
   }
 }
 

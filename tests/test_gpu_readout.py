@@ -52,3 +52,26 @@ def test_fields_are_zero_at_solids_and_written_at_fluid_nodes(core, nsolid, sigm
             assert (t[:, fluid] > 0).all(), key
     for j, t in enumerate(store):  # nothing outside the outputs
         assert torch.isnan(t[:1 + (j % 2)]).all() and torch.isnan(t[1 + (j % 2) + t.numel() - 3:]).all()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx", [1, 31, 32, 33, 255, 256, 257, 511, 512, 513, 1025])
+def test_populations_and_geometry_follow_the_state(core, nx, precision):
+    """The colours add up to the stored f^m (one rounding each of a f + k and b f - k: 4 units of the
+    last place of the largest value), the species are the stored ones, and cos(theta) is the input's."""
+    import torch
+
+    eps = 2.2e-16 if precision == "fp64" else 1.2e-7
+    for nsolid in {0, nx // 3, nx - 1}:
+        solid, theta, sim = _sim(core, (nx, 1, 1), nsolid, precision=precision)
+        fluid = torch.as_tensor(np.flatnonzero(~solid), device="cuda:0")
+        f, _, g = sim.state_parts(sim.get_state())
+        fr, fp, go = sim.populations()
+        assert float((fr[:, fluid] + fp[:, fluid] - f).abs().max()) <= 4 * eps * float(f.abs().max())
+        assert torch.equal(go[:, fluid], g)
+        info, wet = sim.geometry()
+        assert np.abs(wet[3, fluid].double().cpu().numpy() - np.cos(theta[~solid])).max() <= 2 * eps
+        bad = torch.as_tensor(np.flatnonzero(solid), device="cuda:0")
+        for t in (fr, fp, go, wet):
+            assert (t[:, bad] == 0).all()
+        assert ((info.cpu().numpy() >> 18 & 1).astype(bool) == ~solid).all()
