@@ -107,7 +107,8 @@ lbm_status lbm_state_bytes(const lbm_params* params, size_t* bytes);
  *   c0        double initial species concentration; NULL = 1 (ignored without species)
  * d_workspace: device memory of at least lbm_workspace_bytes, 256-byte aligned, owned by the
  * caller and used by the context until lbm_free. stream: hipStream_t or NULL (default stream).
- * The context also holds 40 KB of pinned host memory, where the sums of the steps arrive.
+ * The context also holds 40 KB of pinned host memory, where the sums of the steps arrive; lbm_free, which
+ * neither waits for the device nor disturbs a capture, leaves it to later contexts (16 such blocks are kept).
  * Errors: LBM_ERR_ARG for invalid parameters or inputs (tau <= 0.5, negative sigma/beta/xi,
  * theta outside [0, pi], non-finite values, non-positive mixture density at a fluid node,
  * misaligned or too small workspace, params->fluid_nodes > 0 differing from the mask's fluid

@@ -242,6 +242,7 @@ struct lbm_ctx {
   bool large;            // at least kLargeNodes
   bool ordered;          // fluid-list tiles launched in the order stored at L.order
   double* rows;          // pinned host memory: the ring rows of a chunk, written by k_finish_reduce
+  bool rows_in_use;      // by work that was enqueued and not yet waited for
   void* static_scr;      // device address of the file-scope scratch array on this context's device
   char err[512];
   // Profiling: kEvents events per step of the current chunk (before the first kernel, after each).
@@ -268,6 +269,13 @@ lbm_status fail(lbm_ctx* c, lbm_status s, const char* fmt, ...) {
     hipError_t e_ = (expr);                                                                 \
     if (e_ != hipSuccess) return fail((ctx), LBM_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
+
+// Waits for the context's stream, after which its rows hold what was enqueued to them.
+lbm_status wait_for_rows(lbm_ctx* c) {
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  c->rows_in_use = false;
+  return LBM_OK;
+}
 
 // Message of the last error of a call without a context (lbm_last_error(NULL)), per thread.
 thread_local char g_err[512] = "";
@@ -304,6 +312,47 @@ void* static_scratch(char* msg, size_t len) {
     g_scratch_dev[dev] = ptr;
   }
   return g_scratch_dev[dev];
+}
+
+// Pinned host memory for a context's rows of sums. A freed context leaves its block here for the next one:
+// hipHostFree waits for the whole device and is refused while any stream is captured, and lbm_free, which
+// Python may call at any moment, is to do neither. Blocks are linked through their first bytes; lbm_init,
+// which waits anyway, releases all but kKeptRows of them (40 KB each). The memory is the same from every device.
+constexpr size_t kRowsBytes = 5 * sizeof(double) * kRing;
+constexpr int kKeptRows = 16;
+struct RowsBlock {
+  RowsBlock* next;
+};
+std::mutex g_rows_mu;
+RowsBlock* g_rows = nullptr;
+int g_rows_kept = 0;
+
+RowsBlock* pop_rows(int keep) {
+  std::lock_guard<std::mutex> lock(g_rows_mu);
+  if (g_rows_kept <= keep) return nullptr;
+  RowsBlock* b = g_rows;
+  g_rows = b->next;
+  --g_rows_kept;
+  return b;
+}
+void give_rows(void* rows) {
+  RowsBlock* b = new (rows) RowsBlock;
+  std::lock_guard<std::mutex> lock(g_rows_mu);
+  b->next = g_rows;
+  g_rows = b;
+  ++g_rows_kept;
+}
+hipError_t take_rows(double** rows) {
+  // another stream may be under capture: these calls do not concern it
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  hipError_t e = hipSuccess;
+  void* block = pop_rows(0);
+  if (!block) e = hipHostMalloc(&block, kRowsBytes, hipHostMallocPortable);
+  while (void* spare = pop_rows(kKeptRows)) (void)hipHostFree(spare);
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  *rows = static_cast<double*>(block);
+  return e;
 }
 
 lbm_status check_params(const lbm_params* p, char* msg, size_t len) {
@@ -745,6 +794,7 @@ lbm_status launch_step_from(lbm_ctx* c, const void* src, void* dst, void* fields
 
 // Final reduction of the last step of a chunk (ring row `slot`), and rows 0 .. slot to the host.
 lbm_status launch_finish(lbm_ctx* c, int slot) {
+  c->rows_in_use = true;
   double* ring = reinterpret_cast<double*>(c->ws + c->L.ring);
   hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream,
                      static_cast<const double*>(step_partials(c, slot)), c->nb_pull, ring, slot + 1, c->rows);
@@ -849,7 +899,8 @@ lbm_status launch_init(lbm_ctx* c, const uint8_t* d_solid, const uint8_t* d_reac
   IdWord* ids = reinterpret_cast<IdWord*>(c->ws + c->L.ids);
   // Launch lists: fluid nodes and solid nodes with extrapolated colour, in node order.
   const uint32_t masks[2] = {kFluid, kExtrap};
-  int* lens = reinterpret_cast<int*>(c->rows);  // pinned
+  int* lens = reinterpret_cast<int*>(c->rows);
+  c->rows_in_use = true;
   for (int k = 0; k < 2; ++k) {
     ListNode* list = reinterpret_cast<ListNode*>(c->ws + c->L.lists[k]);
     int* counts = reinterpret_cast<int*>(c->ws + c->L.counts) + k * size_t(c->L.nblocks + 2);
@@ -859,7 +910,7 @@ lbm_status launch_init(lbm_ctx* c, const uint8_t* d_solid, const uint8_t* d_reac
                        k == 0 ? ids : nullptr);
   }
   HIP_TRY(c, hipGetLastError());
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (lbm_status s = wait_for_rows(c); s != LBM_OK) return s;
   c->nfluid = lens[0];
   c->next = lens[1];
   hipLaunchKernelGGL(k_init_wet<R>, dim3(gb), dim3(tb), 0, c->stream, geo, d_solid, info, ids, d_theta, theta_uniform,
@@ -903,12 +954,13 @@ template <int P>
 lbm_status launch_state_sums(lbm_ctx* c, const void* state, double* out) {
   StepArgs<P> A = state ? make_args_from<P>(c, state) : make_args<P>(c, c->cur);
   double* row = reinterpret_cast<double*>(c->ws + c->L.ring);
+  c->rows_in_use = true;
   if (c->nb_fluid)
     hipLaunchKernelGGL(k_state_sums<P>, dim3(c->nb_fluid), dim3(kBlock), 0, c->stream, A);
   hipLaunchKernelGGL(k_finish_reduce, dim3(1), dim3(kBlock), 0, c->stream, static_cast<const double*>(A.partials),
                      c->nb_fluid, row, 1, c->rows);
   HIP_TRY(c, hipGetLastError());
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (lbm_status s = wait_for_rows(c); s != LBM_OK) return s;
   std::copy(c->rows, c->rows + 5, out);
   return LBM_OK;
 }
@@ -1097,9 +1149,8 @@ lbm_status lbm_init(const lbm_params* params, const uint8_t* solid, const double
   // disables that entry point, which reports it.
   c->static_scr = static_scratch(c->err, sizeof(c->err));
   c->err[0] = 0;
-  c->rows = nullptr;
-  if (hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&c->rows), 5 * sizeof(double) * kRing, hipHostMallocDefault);
-      e != hipSuccess) {
+  c->rows_in_use = false;
+  if (hipError_t e = take_rows(&c->rows); e != hipSuccess) {
     snprintf(g_err, sizeof(g_err), "hipHostMalloc: %s", hipGetErrorString(e));
     delete c;
     return LBM_ERR_HIP;
@@ -1153,7 +1204,7 @@ lbm_status lbm_step(lbm_ctx* c, int32_t nsteps, lbm_reductions* per_step) {
       if (lbm_status s = step_once(c, t, nullptr); s != LBM_OK) return s;
     }
     if (lbm_status s = launch_finish(c, chunk - 1); s != LBM_OK) return s;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (lbm_status s = wait_for_rows(c); s != LBM_OK) return s;
     const double* rows = c->rows;
     if (c->prof) {
       for (int t = 0; t < chunk; ++t)
@@ -1376,7 +1427,11 @@ void lbm_free(lbm_ctx* c) {
   if (!c) return;
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
-  if (c->rows) (void)hipHostFree(c->rows);
+  // work that failed before it could be waited for may still write the rows
+  if (c->rows_in_use)
+    (void)hipHostFree(c->rows);
+  else
+    give_rows(c->rows);
   delete c;
 }
 
