@@ -65,25 +65,32 @@ constexpr int kMostSplit = 1;
 // Nontemporal stores of the new populations (0 none, 1 the species', 2 all) where the two states, which
 // alternate, do not fit the 256 MiB last-level cache: a state then leaves it before it is read again, and
 // stored past it leaves the room to what is. A little above the cache's size the species planes alone
-// are, which keeps the rest resident. Measured by the bytes of both states (us per step with none, the
-// species', all): FP32 112^3 169 MB 78, 87, 93; 124^3 230 MB 106, 111, 119; 128^3 253 MB 122, 120, 130; FP64 104^3
-// 271 MB 127, 121, 126; BF16 160^3 295 MB 202, 197, 202; FP32 136^3 302 MB 152, 149, 155; FP64 112^3 339 MB 161, 156,
-// 156; FP32 144^3 359 MB 180, 177, 179; BF16 176^3 392 MB 272, 270, 267; FP32 152^3 422 MB 210, 208, 208; 512 x
-// 512 x 128 4.4 GB 1922 without and 1877 with all. Without species planes the line for all is that of the
-// first measured gain over none.
+// are, which keeps the rest resident. The lines are by the bytes of both states, from cubes of 200 to 450 MB in
+// steps of about 15, porous (half solid) and without solids. Microseconds per step with none, the species', all:
+//   species, lower line: FP32 porous 223 MB 88, 96, 105; 240 MB 105, 101, 110; 258 MB 114, 110, 118; without solids 247 MB
+//     76, 77, 86; 262 MB 86, 80, 90. FP64 porous 226 MB 84, 90, 97; 240 MB 97, 95, 101; without solids 237 MB 72, 72, 80;
+//     265 MB 87, 80, 88. BF16 porous 224 MB 135, 134, 141; 248 MB 155, 151, 160; without solids 225 MB 82, 92, 100; 243
+//     MB 99, 98, 107. FP16 as BF16. (128^3 half solid, 252 MB, is even: 110, 111, 121.)
+//   species, upper line: FP32 porous 358 MB 168, 165, 167; 413 MB 194, 192, 193; 447 MB 212, 209, 208; FP64 337 MB 148,
+//     144, 144; 356 MB 157, 154, 152; BF16 341 MB 225, 223, 224; 379 MB 249, 247, 246.
+//   no species, none and all: FP32 porous 275 MB 143, 143; 292 MB 157, 152; without solids 287 MB 108, 109; 302 MB 116, 113;
+//     FP64 273 MB 132, 132; 287 MB 143, 139; BF16 275 MB 210, 209; 304 MB 237, 234. One-kernel step: FP64 258 MB 59,
+//     67; 273 MB 72, 71; 287 MB 81, 74; FP32 258 MB 64, 72; 275 MB 79, 76; BF16 261 MB 95, 96; 275 MB 104, 101.
 int streams_state(const lbm_params& p, int nfluid) {
   const double s = double(store_bytes(p.precision)), r = double(real_bytes(p.precision));
   const double node = (p.species ? 26 : 19) * s + 4 * r + (p.species && s == 2 ? r : 0);
   const double both = 2 * node * double(nfluid);  // (0.5 million nodes or more, beyond pull_split's smaller lattices)
-  if (both > (p.species ? 370e6 : 320e6)) return 2;
+  if (both > (p.species ? 370e6 : 280e6)) return 2;
   return p.species && both > 248e6 ? 1 : 0;
 }
 // Lattices of which the per-node vectors that one pass leaves to the next (colour scalars, normals) do not
-// stay in the last-level cache either: their stores are nontemporal too. 512 x 512 x 128 (18.4M fluid
-// nodes) FP32 1864 -> 1849 us, FP16 1563 -> 1547, 256^3 (8.4M) FP16 793 -> 787; at 192^3 (3.5M) even, FP64
-// 128^3 (1.05M) loses 0.5%. They also launch the colour, extrap and normal passes in runs of tiles (run_block): 224^3
-// (5.6M) FP32 627 -> 622 us per step, 256^3 FP16 794 -> 787, 512 x 512 x 128 FP32 1882 -> 1858, FP16 1575 -> 1553; 192^3
-// even, 160^3 (2.0M) loses 1.7%, FP64 128^3 0.8%.
+// stay in the last-level cache either: their stores are nontemporal too, and the colour, extrap and normal passes
+// are launched in runs of tiles (run_block). The vectors have the arithmetic type, so FP32 and the 2-byte
+// storages have equal bytes of them per node and gain from about the same count; FP64 from a third of it. One line
+// behind all of them. Microseconds per step without and with, half-solid cubes: FP32 2.6M fluid nodes 285, 288; 3.0M
+// 334, 332; 4.5M 491, 489; 5.5M 605, 600; 12M 1303, 1282. FP16 3.5M 327, 329; 4.0M 379, 377; 4.5M 426, 424; 12M 1125, 1106.
+// FP64 1.0M 200, 204; 1.4M 284, 282; 4.5M 905, 898; 7.0M 1424, 1400. Without solids the gain starts lower (FP32 2.6M 213,
+// 204; FP16 3.5M 217, 214; FP64 0.7M 109, 106) but not evenly (FP32 2.2M 168, 169; without species 483 MB 180, 182).
 constexpr int kLargeNodes = 1 << 22;
 
 struct Layout {

@@ -195,7 +195,8 @@ __device__ inline int logical_block(int skip = 0) {
   const int per_xcd = (gridDim.x - skip) / kXcd, b = blockIdx.x - skip;
   return (b % kXcd) * per_xcd + b / kXcd;
 }
-// The same with runs of kRun tiles dealt to the XCDs in turn (RUNS, large lattices): all XCDs
+// The same with runs of kRun workgroups dealt to the XCDs in turn (RUNS, large lattices; a workgroup is a tile, half
+// a tile in FP64's colour pass): all XCDs
 // then work on one window of the lattice that moves through it, instead of on eight far apart, and what
 // two of them need is still in the last-level cache. Measured against the slabs: 512 x 512 x 128 FP32 colour
 // 568 -> 560 us, extrap 81 -> 79, normal 205 -> 190; 256^3 FP16 normal 104 -> 98, colour 235 -> 234; runs of 8
