@@ -284,7 +284,8 @@ __device__ inline double4 blend(uint32_t m, const double4& a, const double4& b) 
 // unset, 98.9 with this for the words and zeros for the edges, 99.2 with zeros, 100.1 with this for both.
 template <class T>
 __device__ inline void any_value(T& v, int number) {
-  asm("; %1" : "=v"(v) : "n"(number));
+  v = T(0);
+  if (__builtin_constant_p(number)) asm("; %1" : "=v"(v) : "n"(number));  // (zero in builds that do not fold it)
 }
 
 // Entry of a launch list.
