@@ -70,6 +70,8 @@ def run(args):
     w, solid, theta, rr0, rp0 = inputs.workload_inputs(args.workload, device="cuda:0")
     kw = dict(tau=w["tau"], sigma=w["sigma"], beta=w["beta"], xi=w["xi"], accel=[(w["accel"], 0, 0)] * 2,
               species=w["species"], x_open=w["x_open"], tau_species=w["tau_c"], c_inlet=w["c_in"])
+    if args.single_phase:
+        kw.update(sigma=0.0, beta=0.0, xi=0.0, species=False, x_open=False)
     sim = core.Lbm(w["shape"], solid=solid, theta=theta, rho_r0=rr0, rho_p0=rp0, precision=args.precision, **kw)
     sim.step(args.warmup, reductions=False)
     sim.step(args.steps)
@@ -147,20 +149,22 @@ def report(args):
     wr = summarize(args.write, copy_bytes)["counters"]["WRITE_SIZE"]
     fluid = args.fluid_nodes
     adj = args.mode == "adjoint"
-    drv = "python3 -m paper_2608_15781_amd.profile_run %s--precision %s --steps " % (
-        "adjoint " if adj else "--workload %s " % args.workload, args.precision)
+    single = "--single-phase " if args.single_phase else ""
+    drv = "python3 -m paper_2608_15781_amd.profile_run %s--precision %s %s--steps " % (
+        "adjoint " if adj else "--workload %s " % args.workload, args.precision, single)
     steps = (200, 40) if adj else (50, 20)
     title = ("Adjoint kernels, adjoint96 (forward with checkpoints every 20 steps, then the checkpointed backward)"
-             if adj else "Step kernels, %s" % args.workload)
+             if adj else "Step kernels, %s%s" % (args.workload, ", one phase without species (sigma = beta = 0: one kernel "
+                                                 "is the step)" if single else ""))
     lines = ["# %s, %s storage" % (title, args.precision), "",
              "Commands (repository root, `cd /tmp && export TMPDIR=/tmp` first, `PYTHONPATH` = repository root):", "",
              "```",
              "rocprofv3 --kernel-trace --stats --output-format csv -d OUT/prof -o run -- %s%d" % (drv, steps[0]),
              "rocprofv3 --pmc FETCH_SIZE --output-format csv -d OUT/fetch -o run -- %s%d" % (drv, steps[1]),
              "rocprofv3 --pmc WRITE_SIZE --output-format csv -d OUT/write -o run -- %s%d" % (drv, steps[1]),
-             "python3 -m paper_2608_15781_amd.profile_run report %s--precision %s --fluid-nodes %d "
+             "python3 -m paper_2608_15781_amd.profile_run report %s--precision %s %s--fluid-nodes %d "
              "OUT/prof OUT/fetch OUT/write" % ("--mode adjoint " if adj else "--workload %s " % args.workload,
-                                               args.precision, fluid),
+                                               args.precision, single, fluid),
              "```", "",
              "Counter calibration: the run ends with a %d MiB device copy (source evicted from the last-level "
              "cache first); it reads FETCH_SIZE = %.0f KiB and WRITE_SIZE = %.0f KiB for %.0f KiB moved each way, "
@@ -333,6 +337,7 @@ def main():
     ap.add_argument("--mode", default="step", choices=["step", "adjoint"])
     ap.add_argument("--workload", default="bijel128")
     ap.add_argument("--precision", default="fp32")
+    ap.add_argument("--single-phase", action="store_true", help="one colour, no species, sigma = beta = xi = 0")
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--copy-mib", type=int, default=512)
