@@ -322,8 +322,8 @@ void* static_scratch(char* msg, size_t len) {
 }
 
 // Pinned host memory for a context's rows of sums. A freed context leaves its block here for the next one:
-// hipHostFree waits for the whole device and is refused while any stream is captured, and lbm_free, which
-// Python may call at any moment, is to do neither. Blocks are linked through their first bytes; lbm_init,
+// hipHostFree may wait for all work of the device and is not permitted while a stream is under a global capture, and
+// lbm_free, which Python may call at any moment, is to depend on neither. Blocks are linked through their first bytes; lbm_init,
 // which waits anyway, releases all but kKeptRows of them (40 KB each). The memory is the same from every device.
 constexpr size_t kRowsBytes = 5 * sizeof(double) * kRing;
 constexpr int kKeptRows = 16;
